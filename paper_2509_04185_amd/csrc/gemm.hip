@@ -17,17 +17,28 @@
 //   - A workgroup owns a column block of NT tiles (128, 256, or for gate/up 192 columns) and a row block of
 //     MT tiles (up to 128 rows; larger M is cut into row blocks that run on the same XCD
 //     and meet the same weights in its L2), and a range of K steps.
-//   - Weights and activations reach LDS by direct loads (global_load_lds, no registers)
-//     in stages of one K step, a ring of NS stages, so NS - 1 steps are in flight while
-//     the waves multiply the current one.  The four waves split the block into column
-//     quarters (or halves x row halves); a wave reads its weight fragments and the A
-//     fragments (hi and lo) of its rows from LDS and runs two MFMAs per pair.
+//   - Eight waves: four load, four multiply, one of each on a SIMD.  The loading waves bring
+//     weights and activations straight into LDS (global_load_lds, no registers) in stages of
+//     one K step, a ring of NS stages; the multiplying waves split the block into column
+//     halves x row halves, read their weight fragments and the A fragments (hi and lo) of
+//     their rows from LDS and run two MFMAs per pair.  A wave issues in order and a load waits
+//     for room in the memory pipeline at its issue, so a wave that also loads leaves its
+//     matrix core idle for as long; with four waves doing both, gate/up at M = 256 took
+//     117 us (Llama 8B, 28672 x 4096; 72 us of it MFMAs), M = 128 (Qwen 8B, 24576 x 4096)
+//     67 us, and with the loads on waves of their own 98 and 56 us; chained launches over
+//     rotating weights.  Spreading the same loads and reads between the MFMAs of one wave
+//     gave 111 and 74 us; separate rings for weights and activations with up to 14 stages of
+//     weights in flight gained nothing more (94 and 57 us; slower at M <= 64).
+//   - The LDS reads of a row tile's activations are issued one row tile ahead, and a quarter
+//     of the next stage's weight fragments with each, between the MFMAs, so the matrix cores
+//     wait for nothing but the stage barrier.
 //   - When there are too few column blocks to fill the chip, K is split over workgroups
 //     of one XCD, all resident at once (plans of one round): each parks its partial tiles
 //     in that XCD's L2 and waits for the others, then adds the slices of a share of the row
 //     tiles in slice order (deterministic) and runs their epilogue, so the finishing work
-//     of a unit is spread over its slices (e4m3 weights at M <= 32: the last slice to
-//     arrive adds all slices and finishes the block, without waiting).
+//     of a unit is spread over its slices, and in a slice over its four multiplying waves
+//     (each a quarter of a row tile's columns, all slices' pieces in flight at once: O
+//     projection at M = 32 13.4 -> 11.5 us with the loading waves, 12.4 without this).
 // Epilogues (acc in the MFMA D layout: lane l holds column l % 16 of a tile, rows
 // 4*(l/16) + i):
 //   EPI_SCALED_STORE  out = rinv[m] * y           (QKV projection, LM head)
@@ -52,8 +63,8 @@ namespace sbd {
 
 template <int MT, int NT, bool W8>
 struct MidCfg {
-  // waves across the column block: 2 x 2 waves (each reads half the activation and half the
-  // weight fragments of a stage from LDS: 16 KB per 16-tile stage, against 20 KB in a 4 x 1 split)
+  // multiplying waves across the column block: 2 x 2 waves (each reads half the activation and half
+  // the weight fragments of a stage from LDS: 16 KB per 16-tile stage, against 20 KB in a 4 x 1 split)
   static constexpr int WC = 2;
   static constexpr int WM = 4 / WC;            // waves across the row block
   static constexpr int CW = NT / WC;           // tiles per wave
@@ -64,10 +75,10 @@ struct MidCfg {
   static constexpr int NWL = WB / 1024;               // weight wave-loads per stage
   static constexpr int STAGE = WB + 2 * MT * 1024;    // one K step: weights + 2 MT A fragments
   static constexpr int NS = (144 * 1024) / STAGE > 8 ? 8 : (144 * 1024) / STAGE;  // ring stages
-  static constexpr int FPW = (NWL + 2 * MT) / 4;      // wave-loads of each wave per stage
+  static constexpr int FPW = (NWL + 2 * MT) / 4;      // wave-loads of each loading wave per stage
   static constexpr int NWU = NWL / 4;                 // of a wave's FPW loads, the first NWU are weights
   static_assert(MTW >= 1 && (NWL + 2 * MT) % 4 == 0 && NWL % 4 == 0, "unsupported tile shape");
-  static_assert((NS - 1) * FPW <= 63, "vmcnt range");
+  static_assert(NS >= 3 && (NS - 1) * FPW <= 63, "vmcnt range");
 };
 
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{})
@@ -142,12 +153,13 @@ __device__ __forceinline__ void slices_arrived(const GemmArgs& a, int* ctr, int 
   __syncthreads();
 }
 
-// STREAM: every weight byte is read by one workgroup (one row block): non-temporal loads.
+// SPLIT: K is split over a.splits workgroups (kernels of their own: without the other case's
+// epilogue the accumulators are dead once parked, and the slices' sums get their registers).
 // W8: the weights are e4m3 bytes (a.Wp8, per-row scales a.wscale) in the same packing, one
 // byte per element; a fragment is widened to the bf16 MFMA operand (times its row's scale,
 // exact) after its LDS read, so the products are those of the widened bf16 matrix.
-template <int MT, int NT, int EPI, bool STREAM, bool W8>
-__global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
+template <int MT, int NT, int EPI, bool W8, bool SPLIT>
+__global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   using Cfg = MidCfg<MT, NT, W8>;
   constexpr int WC = Cfg::WC, CW = Cfg::CW, MTW = Cfg::MTW, NS = Cfg::NS, FPW = Cfg::FPW;
   constexpr int STAGE = Cfg::STAGE;
@@ -156,9 +168,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   typedef typename std::conditional<W8, i32x2, i32x4>::type WFr;  // a weight fragment in registers
   __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
   __shared__ float rinv_s[MT * 16];
-  __shared__ float ssq_s[WC][MT * 16];
+  __shared__ float ssq_s[4][MT * 16];
 
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = w8 & 3;
   const int r = lane & 15, g = lane >> 4;
   const int wc = w % WC, wm = w / WC;
 
@@ -179,51 +191,67 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   const int nst = s_e - s_b;
   const int t0 = cb * NT;
 
-  // Sources of this wave's loads: load u of a stage fills 1 KB f = w + 4u of it; f < NWL is
-  // weight tile t0 + f (bf16) or the tiles t0 + 2f, t0 + 2f + 1 (e4m3: their fragments are
-  // adjacent in the packing), else A fragment f - NWL = 2 * (row tile) + (0: hi, 1: lo).
-  const char* src[FPW];
-  int64_t stride[FPW];
+  auto bar = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  if (w8 >= 4) {
+    // ---- loading wave: load u of a stage fills 1 KB f = w + 4u of it; f < NWL is weight tile
+    // t0 + f (bf16) or the tiles t0 + 2f, t0 + 2f + 1 (e4m3: their fragments are adjacent in
+    // the packing), else A fragment f - NWL = 2 * (row tile) + (0: hi, 1: lo).
+    constexpr int64_t kWStep = W8 ? kPackStep : kPackStep * 2;
+    const char* src[FPW];
+    const int64_t a_step = (int64_t)a.a_mtiles * 1024;
 #pragma unroll
-  for (int u = 0; u < FPW; ++u) {
-    const int f = w + 4 * u;
-    if (u < NWU) {
-      if constexpr (W8) {
-        src[u] = (const char*)(a.Wp8 + packed_frag(t0 + 2 * f, s_b, S_all) + lane * 16);
-        stride[u] = kPackStep;
+    for (int u = 0; u < FPW; ++u) {
+      const int f = w + 4 * u;
+      if (u < NWU) {
+        if constexpr (W8) {
+          src[u] = (const char*)(a.Wp8 + packed_frag(t0 + 2 * f, s_b, S_all)) + lane * 16;
+        } else {
+          // a half-full block's tiles past the end read the last tile (results discarded)
+          constexpr bool kHalf = EPI == EPI_SCALED_STORE || EPI == EPI_LOGITS_EB;
+          src[u] = (const char*)(a.Wp + packed_frag(kHalf ? min(t0 + f, a.n_tiles - 1) : t0 + f, s_b, S_all)) + lane * 16;
+        }
       } else {
-        // a half-full block's tiles past the end read the last tile (results discarded)
-        constexpr bool kHalf = EPI == EPI_SCALED_STORE || EPI == EPI_LOGITS_EB;
-        src[u] = (const char*)(a.Wp + packed_frag(kHalf ? min(t0 + f, a.n_tiles - 1) : t0 + f, s_b, S_all) + lane * 8);
-        stride[u] = kPackStep * 2;
-      }
-    } else {
-      const int ai = f - Cfg::NWL;
-      int row = row0 + (ai >> 1) * 16 + r;
-      if (row >= a.M) row = a.M - 1;  // rows past the end: valid data, results discarded
-      const bf16_t* base = (ai & 1) ? a.A_lo : a.A;
-      if (a.a_mtiles) {  // fragment order: one contiguous 1 KB per fragment
-        src[u] = (const char*)(base + apack(a.a_row0 + row, (int64_t)s_b * 32 + g * 8, a.a_mtiles));
-        stride[u] = (int64_t)a.a_mtiles * 1024;
-      } else {
-        src[u] = (const char*)(base + (int64_t)row * a.lda + (int64_t)s_b * 32 + g * 8);
-        stride[u] = 64;
+        const int ai = f - Cfg::NWL;
+        const int row = min(row0 + (ai >> 1) * 16 + r, a.M - 1);  // rows past the end: valid data, results discarded
+        src[u] = (const char*)(((ai & 1) ? a.A_lo : a.A) + apack(a.a_row0 + row, (int64_t)s_b * 32 + g * 8, a.a_mtiles));
       }
     }
+    int slot = w * 1024;
+    auto issue = [&](auto NT_) {
+      constexpr int kPolW = decltype(NT_)::value ? 2 : 0;  // nt: read once
+#pragma unroll
+      for (int u = 0; u < FPW; ++u) {
+        if (u < NWU)
+          __builtin_amdgcn_global_load_lds((const void*)src[u], (__attribute__((address_space(3))) void*)(smem + slot + u * 4096), 16, 0, kPolW);
+        else
+          __builtin_amdgcn_global_load_lds((const void*)src[u], (__attribute__((address_space(3))) void*)(smem + slot + u * 4096), 16, 0, 0);
+        src[u] += u < NWU ? kWStep : a_step;
+      }
+      slot = slot + STAGE >= NS * STAGE ? slot + STAGE - NS * STAGE : slot + STAGE;
+    };
+    auto load = [&](auto NT_) {
+#pragma unroll 1
+      for (int st = 0; st < NS && st < nst; ++st) issue(NT_);
+      vm_wait_stages<FPW, NS - 1>(min(NS - 1, nst - 1));  // stage 0 has landed
+      bar();
+      // barrier c: stage c + 1 has landed; every wave is done with stage c - 1, whose slot
+      // takes stage c - 1 + NS
+#pragma unroll 1
+      for (int c = 0; c + 1 < nst; ++c) {
+        vm_wait_stages<FPW, NS - 2>(min(nst, max(NS, c - 1 + NS)) - 2 - c);
+        bar();
+        if (c >= 1 && c - 1 + NS < nst) issue(NT_);
+      }
+    };
+    // one row block: every weight byte is read by one workgroup, non-temporal
+    if (MB == 1) load(std::true_type{});
+    else load(std::false_type{});
+    return;  // a wave that has ended no longer counts at the workgroup's barriers
   }
-  // stage st into ring slot st % NS
-  auto issue = [&](int st) {
-    char* dst = smem + (st % NS) * STAGE + w * 1024;
-    constexpr int kPolW = STREAM ? 2 : 0;  // nt: read once
-#pragma unroll
-    for (int u = 0; u < NWU; ++u)
-      __builtin_amdgcn_global_load_lds((const void*)(src[u] + st * stride[u]),
-                                       (__attribute__((address_space(3))) void*)(dst + u * 4096), 16, 0, kPolW);
-#pragma unroll
-    for (int u = NWU; u < FPW; ++u)
-      __builtin_amdgcn_global_load_lds((const void*)(src[u] + st * stride[u]),
-                                       (__attribute__((address_space(3))) void*)(dst + u * 4096), 16, 0, 0);
-  };
 
   f32x4 acc[MTW][CW];
 #pragma unroll
@@ -234,9 +262,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   // LDS reads of a stage with ds_read16 (sbd_device.h): the compiler would otherwise guard
   // every read of LDS with a wait for all direct loads in flight (it cannot tell the ring
   // slots apart), draining the ring at each step.  Ordering is explicit instead: the stage
-  // barrier before the reads, lds_wait() after them, and the results pinned behind it.
-  // The reads of stage c + 1 are issued before the MFMAs of stage c (two register sets), so
-  // the LDS traffic of one step overlaps the matrix work of the previous one.
+  // barrier before the reads, a wait after them, and the results pinned behind it.  The
+  // weights of a stage are read during the stage before (two register sets), its activations
+  // one row tile ahead, so LDS reads overlap the matrix work.
   constexpr int WFB = W8 ? 512 : 1024;  // bytes of one weight fragment in LDS
   const uint32_t lds_w = (uint32_t)(uintptr_t)smem + (uint32_t)(wc * CW * WFB + lane * (WFB / 64));
   const uint32_t lds_a = (uint32_t)(uintptr_t)smem + (uint32_t)(WB + wm * MTW * 2048 + lane * 16);
@@ -244,46 +272,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   float wsc[CW];
 #pragma unroll
   for (int cw = 0; cw < CW; ++cw) wsc[cw] = W8 ? a.wscale[(int64_t)(t0 + wc * CW + cw) * 16 + r] : 1.0f;
-  auto read_frags = [&](int st, WFr (&wv)[CW], i32x4 (&av)[MTW][2]) {
-    const uint32_t sb = (uint32_t)((st % NS) * STAGE);
-    const uint32_t aw = lds_w + sb, aa = lds_a + sb;
-    static_for<CW>([&](auto I) {
-      if constexpr (W8) wv[decltype(I)::value] = ds_read8<decltype(I)::value * 512>(aw);
-      else wv[decltype(I)::value] = ds_read16<decltype(I)::value * 1024>(aw);
-    });
-    static_for<MTW * 2>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      av[i / 2][i % 2] = ds_read16<i * 1024>(aa);
-    });
-  };
-  auto pin_frags = [&](WFr (&wv)[CW], i32x4 (&av)[MTW][2]) {
-#pragma unroll
-    for (int cw = 0; cw < CW; ++cw) lds_pin(wv[cw]);
-#pragma unroll
-    for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) lds_pin(av[mw][h]);
-  };
-  auto mfma_frags = [&](const WFr (&wv)[CW], const i32x4 (&av)[MTW][2]) {
-    if constexpr (W8) {  // each fragment widened once; every accumulator still takes hi, then lo
-#pragma unroll
-      for (int cw = 0; cw < CW; ++cw) {
-        const i32x4 wf = e4m3x8_to_bf16(wv[cw], wsc[cw]);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int mw = 0; mw < MTW; ++mw) acc[mw][cw] = mfma16x16x32(av[mw][h], wf, acc[mw][cw]);
-      }
-    } else {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-          for (int cw = 0; cw < CW; ++cw) acc[mw][cw] = mfma16x16x32(av[mw][h], wv[cw], acc[mw][cw]);
-    }
-  };
-
+  int rslot = 0;  // ring slot (bytes) of the current stage
   // Consumers of a norm: the producer's partial sums of squares of this block's rows,
   // requested before the stream (thread t adds partials of row t / TPR, float4 at a time).
   constexpr int TPR = 256 / (MT * 16);
@@ -301,88 +290,116 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
     pre[j] = (norm_in && vec4 && m_t < a.M && p4 < n4) ? prow[p4] : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // A kernel's code runs cold from the instruction cache in every workgroup: the ring is
-  // driven by compact loops (slot = stage % NS at run time) rather than unrolled code.
-  // NS stages in flight: stage c's slot is refilled once every wave holds its fragments.
-#pragma unroll 1
-  for (int st = 0; st < NS && st < nst; ++st) issue(st);
-  WFr wv0[CW], wv1[CW];
-  i32x4 av0[MTW][2], av1[MTW][2];
-  vm_wait_stages<FPW, NS - 1>(min(NS - 1, nst - 1));  // stage 0 has landed (this wave's part)
-  stage_barrier();                                    // ... and every wave's
-  read_frags(0, wv0, av0);
-  lds_wait();
-  pin_frags(wv0, av0);
-  // step c: the fragments of stage c are in registers; stage c + 1 is read meanwhile
-  auto step = [&](int c, WFr (&wc_)[CW], i32x4 (&ac_)[MTW][2], WFr (&wn)[CW], i32x4 (&an)[MTW][2]) {
-    if (c + 1 < nst) {
-      vm_wait_stages<FPW, NS - 2>(min(NS - 2, nst - 2 - c));  // stage c + 1 has landed (this wave's part)
-      stage_barrier();  // ... and every wave's; every wave holds stage c's fragments: its slot is free
-      if (c + NS < nst) issue(c + NS);
-      read_frags(c + 1, wn, an);
+  // The epilogue's share of a wave.  One slice: the wave's own accumulators, CW tiles of MTW
+  // row tiles.  Split: a quarter of the columns of each of the slice's row tiles (a half of
+  // every second one for EB statistics, whose 64-column chunks stay inside one wave).
+  constexpr bool kQuarter = SPLIT && EPI != EPI_LOGITS_EB;
+  constexpr int CWE = kQuarter ? NT / 4 : CW;   // tiles of a row tile
+  constexpr int CPR = CWE * 4;                  // float4 pieces of a row
+  constexpr int NPASS = 16 * CPR / 64;          // read-back passes per row tile
+  const int ct0 = kQuarter ? w * CWE : wc * CW;  // first tile in the block
+  const int n_w0 = (t0 + ct0) * 16;              // first output column
+  const int n_l = n_w0 + (lane % CPR) * 4;
+  f32x4 xcur[NPASS], xnxt[NPASS];
+  i32x2 gw{0, 0};
+  // EPI_RESID: a lane's residual pieces of the next row tile are requested before the stores
+  // of the current one; the gain is the same for every row of the lane
+  auto load_x = [&](int rt, f32x4(&xv)[NPASS]) {
+#pragma unroll
+    for (int j = 0; j < NPASS; ++j) {
+      const int m = row0 + rt * 16 + (j * 64 + lane) / CPR;
+      xv[j] = *(const f32x4*)(a.x + (int64_t)min(m, a.M - 1) * a.ldx + n_l);  // rows past the end: never stored
     }
-    // the MFMAs stay between the reads and their wait (they do not touch memory, so the
-    // compiler would otherwise move them past the wait)
+  };
+  if constexpr (SPLIT && EPI == EPI_RESID) {  // the first row tile's, ahead of the stream: nothing of these depends on it
+    gw = *(const i32x2*)(a.g_next + n_l);
+    load_x(min(kc, MT - 1), xcur);
+  }
+
+  WFr wv0[CW], wv1[CW];
+  i32x4 av[2][2];  // [row tile parity][hi, lo]
+  bar();  // stage 0 is in
+  static_for<CW>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    if constexpr (W8) wv0[i] = ds_read8<i * 512>(lds_w);
+    else wv0[i] = ds_read16<i * 1024>(lds_w);
+  });
+  av[0][0] = ds_read16<0>(lds_a);
+  av[0][1] = ds_read16<1024>(lds_a);
+  lds_wait();
+#pragma unroll
+  for (int i = 0; i < CW; ++i) lds_pin(wv0[i]);
+  lds_pin(av[0][0]);
+  lds_pin(av[0][1]);
+  constexpr int WPM = (CW + MTW - 1) / MTW;  // weight reads per row tile
+  // step cc: MFMAs of stage cc; every accumulator takes hi, then lo (e4m3 fragments are
+  // widened once per row tile).  P0: parity of the register pair holding row tile 0.
+  auto step = [&](auto P0, int cc, WFr (&wc_)[CW], WFr (&wn)[CW]) {
+    if (cc + 1 < nst) bar();
+    const int nslot = rslot + STAGE == NS * STAGE ? 0 : rslot + STAGE;
     __builtin_amdgcn_sched_barrier(0);
-    mfma_frags(wc_, ac_);
-    __builtin_amdgcn_sched_barrier(0);
-    lds_wait();
-    pin_frags(wn, an);
+    static_for<MTW>([&](auto MW) {
+      constexpr int mw = decltype(MW)::value, p = (mw + decltype(P0)::value) & 1, q = p ^ 1;
+      constexpr int wleft = CW - mw * WPM, nw = wleft < 0 ? 0 : (wleft < WPM ? wleft : WPM);  // weight reads here
+      constexpr bool kNext = mw + 1 == MTW;
+      constexpr int NM = 2 * CW;
+      i32x4 wide;
+      static_for<NM>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        // reads: the next row tile's hi and lo, then this row tile's share of the next stage's weights
+        if constexpr (i == 0) av[q][0] = kNext ? ds_read16<0>(lds_a + nslot) : ds_read16<(mw + 1) * 2048>(lds_a + rslot);
+        if constexpr (i == 1) av[q][1] = kNext ? ds_read16<1024>(lds_a + nslot) : ds_read16<(mw + 1) * 2048 + 1024>(lds_a + rslot);
+        if constexpr (i >= 2 && i < 2 + WPM && mw * WPM + i - 2 < CW) {
+          constexpr int x = mw * WPM + i - 2;
+          if constexpr (W8) wn[x] = ds_read8<x * 512>(lds_w + nslot);
+          else wn[x] = ds_read16<x * 1024>(lds_w + nslot);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (W8) {
+          constexpr int cw = i / 2, h = i % 2;
+          if constexpr (h == 0) wide = e4m3x8_to_bf16(wc_[cw], wsc[cw]);
+          acc[mw][cw] = mfma16x16x32(av[p][h], wide, acc[mw][cw]);
+        } else {
+          constexpr int h = i / CW, cw = i % CW;
+          acc[mw][cw] = mfma16x16x32(av[p][h], wc_[cw], acc[mw][cw]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (kNext) {
+        lds_wait();
+#pragma unroll
+        for (int i = 0; i < CW; ++i) lds_pin(wn[i]);
+      } else {
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(nw) : "memory");
+      }
+      lds_pin(av[q][0]);
+      lds_pin(av[q][1]);
+    });
+    rslot = nslot;
   };
 #pragma unroll 1
   for (int c = 0; c < nst; c += 2) {
-    step(c, wv0, av0, wv1, av1);
-    if (c + 1 < nst) step(c + 1, wv1, av1, wv0, av0);
+    step(std::integral_constant<int, 0>{}, c, wv0, wv1);
+    if (c + 1 < nst) step(std::integral_constant<int, MTW & 1>{}, c + 1, wv1, wv0);
   }
 
   // ---- K split over workgroups (a plan of one round: every slice of a unit is resident):
   // each slice parks its partial tiles and waits for the others; the epilogue then adds the
   // slices of the row tiles kc, kc + KS, ... of the block in slice order and finishes them
-  // (every output is the same sum of the same slices, whichever slice finishes it).  The
-  // accumulators are not written again after the K loop: the sums go straight to LDS.
-  // e4m3 weights and two row tiles (M <= 32) keep the single finisher: the last slice to
-  // arrive sums every slice into the accumulators and finishes the whole block (there the
-  // shared sums made the compiler move accumulators between register files inside the K
-  // loop, which cost more than the shared finishing saves)
-  constexpr bool kSingle = W8 && MT == 2;
-  auto own = [&](int rt) { return kSingle || rt % KS == kc; };
-  const int64_t slot = ((int64_t)uid * 4 + w) * (MTW * CW);       // in 1 KB (64 x f32x4) pieces
-  const int64_t zstride = (int64_t)n_cb * MB * 4 * MTW * CW;       // pieces per slice
-  if (KS > 1) {
+  // (every output is the same sum of the same slices, whichever slice finishes it).
+  auto own = [&](int rt) { return !SPLIT || rt % KS == kc; };
+  const int64_t zstride = (int64_t)n_cb * MB * 4 * MTW * CW;       // 1 KB (64 x f32x4) pieces per slice
+  const int64_t uslot = (int64_t)uid * 4 * (MTW * CW);
+  if constexpr (SPLIT) {
 #pragma unroll
     for (int mw = 0; mw < MTW; ++mw)
 #pragma unroll
       for (int cw = 0; cw < CW; ++cw)
-        *(f32x4*)(a.part + ((kc * zstride + slot + mw * CW + cw) * 64 + lane) * 4) = acc[mw][cw];
-    if constexpr (kSingle) {
-      if (!last_arrival_xcd(a.counters + (int64_t)uid * kCtrStride, KS)) return;
-      // ZB slices at a time, every piece of a slice in flight together; added in slice order
-      constexpr int ZB = MTW * CW >= 32 ? 1 : (MTW * CW >= 16 ? 2 : 4);
-      const __amdgpu_buffer_rsrc_t rp = buf_rsrc(a.part);
-#pragma unroll
-      for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-        for (int cw = 0; cw < CW; ++cw) acc[mw][cw] = f32x4{0.f, 0.f, 0.f, 0.f};
-      for (int z0 = 0; z0 < KS; z0 += ZB) {
-        i32x4 v[ZB][MTW][CW];
-#pragma unroll
-        for (int zz = 0; zz < ZB; ++zz)
-#pragma unroll
-          for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-            for (int cw = 0; cw < CW; ++cw)
-              v[zz][mw][cw] = z0 + zz < KS ? ld16_l2(rp, (uint32_t)((((z0 + zz) * zstride + slot + mw * CW + cw) * 64 + lane) * 16))
-                                           : i32x4{0, 0, 0, 0};
-#pragma unroll
-        for (int zz = 0; zz < ZB; ++zz)
-#pragma unroll
-          for (int mw = 0; mw < MTW; ++mw)
-#pragma unroll
-            for (int cw = 0; cw < CW; ++cw) acc[mw][cw] += __builtin_bit_cast(f32x4, v[zz][mw][cw]);
-      }
-    } else {
-      slices_arrived(a, a.counters + (int64_t)uid * kCtrStride, KS, 65536 + EPI);
-    }
+        *(f32x4*)(a.part + ((kc * zstride + uslot + (w * MTW + mw) * CW + cw) * 64 + lane) * 4) = acc[mw][cw];
+    slices_arrived(a, a.counters + (int64_t)uid * kCtrStride, KS, 65536 + EPI);
+  } else if constexpr (EPI == EPI_RESID) {
+    gw = *(const i32x2*)(a.g_next + n_l);
+    load_x(wm * MTW, xcur);
   }
 
   // ---- 1/rms of the block's rows (partials beyond the prefetched ones read here)
@@ -407,148 +424,149 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
   __syncthreads();  // rinv_s written; every wave is past the ring, which now stages results
 
   // ---- epilogue.  Each wave passes its tiles through LDS one row tile at a time (16 rows x
-  // 16 CW columns, rows padded by 4 floats), then lanes own 4 consecutive columns of a row:
-  // a row's 16 CW columns are written by consecutive lanes as whole 16-byte pieces.
-  constexpr int LDR = CW * 16 + 4;  // staged row length (floats)
-  constexpr int CPR = CW * 4;       // float4 pieces per staged row
+  // 16 CWE columns, rows padded by 4 floats), then lanes own 4 consecutive columns of a row:
+  // a row's 16 CWE columns are written by consecutive lanes as whole 16-byte pieces.
+  constexpr int LDR = CWE * 16 + 4;  // staged row length (floats)
   float* stg = reinterpret_cast<float*>(smem) + w * 16 * LDR;
-  const int n_w0 = (t0 + wc * CW) * 16;  // first output column of this wave
   // false only for the empty half of a half-full block (an LM head's last block)
   const bool cols_in = (EPI != EPI_SCALED_STORE && EPI != EPI_LOGITS_EB) || n_w0 < a.n_tiles * 16;
-  // EPI_RESID: a lane's residual pieces of row tile mw + 1 are requested before the stores
-  // of row tile mw (which the compiler may not move them past); the gain is the same for
-  // every row of the lane.
-  constexpr int NPASS = 16 * CPR / 64;  // read-back passes per row tile
-  const int n_l = n_w0 + (lane % CPR) * 4;
-  f32x4 xcur[NPASS], xnxt[NPASS];
-  i32x2 gw{0, 0};
-  auto load_x = [&](int mw, f32x4(&xv)[NPASS]) {
+  auto finish = [&](int rt, const f32x4 (&y_)[CWE], const f32x4 (&xv_)[NPASS]) {
+    const int rl0 = rt * 16;  // first local row of the row tile
 #pragma unroll
-    for (int j = 0; j < NPASS; ++j) {
-      const int m = row0 + (wm * MTW + mw) * 16 + (j * 64 + lane) / CPR;
-      xv[j] = m < a.M ? *(const f32x4*)(a.x + (int64_t)m * a.ldx + n_l) : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int cw = 0; cw < CWE; ++cw)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) stg[(4 * g + i) * LDR + cw * 16 + r] = y_[cw][i];
+    if constexpr (EPI == EPI_SWIGLU) {
+      // task: (row, tile tt, half h) -> act columns 8 (tile) + 4 h .. + 3
+      constexpr int NT2 = 16 * CWE * 2;
+#pragma unroll
+      for (int j = 0; j < (NT2 + 63) / 64; ++j) {
+        const int idx = j * 64 + lane;
+        const int row = idx / (CWE * 2), tt = (idx % (CWE * 2)) >> 1, h = idx & 1;
+        const int m = row0 + rl0 + row;
+        if (idx < NT2 && m < a.M) {
+          const f32x4 gt = *(const f32x4*)(stg + row * LDR + tt * 16 + h * 4);
+          const f32x4 up = *(const f32x4*)(stg + row * LDR + tt * 16 + 8 + h * 4);
+          const float rv = rinv_s[rl0 + row];
+          f32x4 y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float gv = gt[e] * rv;
+            y[e] = gv / (1.0f + expf(-gv)) * (up[e] * rv);
+          }
+          i32x2 hi, lo;
+          split_bf16x4(y, hi, lo);
+          const int64_t o = aoff(m, (int64_t)(t0 + ct0 + tt) * 8 + h * 4, a.ld_act, a.o_mtiles);
+          *(i32x2*)(a.act + o) = hi;
+          *(i32x2*)(a.act_lo + o) = lo;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NPASS; ++j) {
+        const int idx = j * 64 + lane;
+        const int row = idx / CPR, pc = idx % CPR;
+        const int m = row0 + rl0 + row;
+        const int n = n_w0 + pc * 4;
+        const f32x4 y = *(const f32x4*)(stg + row * LDR + pc * 4);
+        if constexpr (EPI == EPI_SCALED_STORE) {
+          if (m < a.M) *(f32x4*)(a.out_f32 + (int64_t)m * a.ldo + n) = y * rinv_s[rl0 + row];
+        } else if constexpr (EPI == EPI_LOGITS_EB) {
+          if (m < a.M && a.out_f32 != nullptr) *(f32x4*)(a.out_f32 + (int64_t)m * a.ldo + n) = y * rinv_s[rl0 + row];
+        } else {  // EPI_RESID
+          float s2 = 0.f;
+          if (m < a.M) {
+            const f32x4 xv = xv_[j] + y;
+            *(f32x4*)(a.x + (int64_t)m * a.ldx + n) = xv;
+            f32x4 xg;
+            xg[0] = xv[0] * __uint_as_float((uint32_t)gw[0] << 16);
+            xg[1] = xv[1] * __uint_as_float((uint32_t)gw[0] & 0xffff0000u);
+            xg[2] = xv[2] * __uint_as_float((uint32_t)gw[1] << 16);
+            xg[3] = xv[3] * __uint_as_float((uint32_t)gw[1] & 0xffff0000u);
+            i32x2 hi, lo;
+            split_bf16x4(xg, hi, lo);
+            const int64_t on = aoff(m, n, a.ldx, a.o_mtiles);
+            *(i32x2*)(a.xn + on) = hi;
+            *(i32x2*)(a.xn_lo + on) = lo;
+            s2 = (xv[0] * xv[0] + xv[1] * xv[1]) + (xv[2] * xv[2] + xv[3] * xv[3]);
+          }
+#pragma unroll
+          for (int o = 1; o < CPR; o <<= 1) s2 += __shfl_xor(s2, o);  // the row's CPR lanes
+          if (pc == 0) ssq_s[kQuarter ? w : wc][rl0 + row] = s2;
+        }
+      }
+    }
+    if constexpr (EPI == EPI_LOGITS_EB) {
+      // the staged row tile again: lane L reduces VPL = 4 CW consecutive columns of row L / 4,
+      // 16 / CW lanes per 64-column chunk
+      constexpr int VPL = 4 * CW, LPC = 16 / CW;
+      static_assert(VPL * LPC == kEbFChunk, "a chunk is 64 columns");
+      const int row = lane >> 2, seg = lane & 3;
+      const int m = row0 + rl0 + row;
+      const int col0 = n_w0 + seg * VPL;
+      float mx;
+      int arg;
+      double z, sz;
+      eb_seg_stats<VPL, LPC>(stg + row * LDR + seg * VPL, rinv_s[rl0 + row], col0, a.eb_mask_id, mx, arg, z, sz);
+      if (seg % LPC == 0 && m < a.M) eb_chunk_store(a.eb_part, a.eb_arg, a.eb_chunks, m, col0 / kEbFChunk, mx, arg, z, sz);
     }
   };
-  if constexpr (EPI == EPI_RESID) {
-    gw = *(const i32x2*)(a.g_next + n_l);
-    if (own(wm * MTW)) load_x(0, xcur);
-  }
+  if constexpr (SPLIT) {
+    const __amdgpu_buffer_rsrc_t rp = buf_rsrc(a.part);
+    // the slices' sum of this wave's tiles of row tile rt: NZ slices' pieces in flight at once
+    // (indices past the last slice re-read it), added in slice order
+    auto add_slices = [&](auto NZ_, int rt, int z0, f32x4 (&sum)[CWE]) {
+      constexpr int NZ = decltype(NZ_)::value;
+      i32x4 v[NZ][CWE];
 #pragma unroll
-  for (int mw = 0; mw < MTW; ++mw) {
-    const int rl0 = (wm * MTW + mw) * 16;  // first local row of this row tile
-    if constexpr (EPI == EPI_RESID) {
-      if (mw + 1 < MTW && own(wm * MTW + mw + 1)) load_x(mw + 1, xnxt);
-    }
-    if (own(wm * MTW + mw) && cols_in) {
-      if (!kSingle && KS > 1) {
-        // the slices' sums of this wave's tiles of the row tile: ZR slices at a time, all
-        // their pieces in flight
-        constexpr int ZR = 4;
-        const __amdgpu_buffer_rsrc_t rp = buf_rsrc(a.part);
-        f32x4 sum[CW];
+      for (int zz = 0; zz < NZ; ++zz)
 #pragma unroll
-        for (int cw = 0; cw < CW; ++cw) sum[cw] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int z0 = 0; z0 < KS; z0 += ZR) {
-          i32x4 v[ZR][CW];
-#pragma unroll
-          for (int zz = 0; zz < ZR; ++zz)
-#pragma unroll
-            for (int cw = 0; cw < CW; ++cw)
-              v[zz][cw] = z0 + zz < KS ? ld16_l2(rp, (uint32_t)((((z0 + zz) * zstride + slot + mw * CW + cw) * 64 + lane) * 16))
-                                       : i32x4{0, 0, 0, 0};
-#pragma unroll
-          for (int zz = 0; zz < ZR; ++zz)
-#pragma unroll
-            for (int cw = 0; cw < CW; ++cw) sum[cw] += __builtin_bit_cast(f32x4, v[zz][cw]);
+        for (int i = 0; i < CWE; ++i) {
+          const int ct = ct0 + i;  // tile of the block -> the wave that parked it
+          const int pw = (rt / MTW) * WC + ct / CW;
+          const int64_t piece = (int64_t)min(z0 + zz, KS - 1) * zstride + uslot + (pw * MTW + rt % MTW) * CW + ct % CW;
+          v[zz][i] = ld16_l2(rp, (uint32_t)((piece * 64 + lane) * 16));
         }
 #pragma unroll
-        for (int cw = 0; cw < CW; ++cw)
+      for (int zz = 0; zz < NZ; ++zz)
+        if (z0 + zz < KS) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) stg[(4 * g + i) * LDR + cw * 16 + r] = sum[cw][i];
-      } else {
-#pragma unroll
-        for (int cw = 0; cw < CW; ++cw)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) stg[(4 * g + i) * LDR + cw * 16 + r] = acc[mw][cw][i];
+          for (int i = 0; i < CWE; ++i) sum[i] += __builtin_bit_cast(f32x4, v[zz][i]);
+        }
+    };
+    constexpr int NZ = CWE >= 8 ? 4 : 8;
+#pragma unroll 1
+    for (int rt = kc; rt < MT; rt += KS) {
+      if constexpr (EPI == EPI_RESID) {
+        if (rt + KS < MT) load_x(rt + KS, xnxt);
       }
-      if constexpr (EPI == EPI_SWIGLU) {
-        // task: (row, tile tt, half h) -> act columns 8 (tile) + 4 h .. + 3
-        constexpr int NT2 = 16 * CW * 2;
+      if (cols_in && (kQuarter || ((rt - kc) / KS) % Cfg::WM == wm)) {
+        f32x4 sum[CWE];
 #pragma unroll
-        for (int j = 0; j < (NT2 + 63) / 64; ++j) {
-          const int idx = j * 64 + lane;
-          const int row = idx / (CW * 2), tt = (idx % (CW * 2)) >> 1, h = idx & 1;
-          const int m = row0 + rl0 + row;
-          if (idx < NT2 && m < a.M) {
-            const f32x4 gt = *(const f32x4*)(stg + row * LDR + tt * 16 + h * 4);
-            const f32x4 up = *(const f32x4*)(stg + row * LDR + tt * 16 + 8 + h * 4);
-            const float rv = rinv_s[rl0 + row];
-            f32x4 y;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float gv = gt[e] * rv;
-              y[e] = gv / (1.0f + expf(-gv)) * (up[e] * rv);
-            }
-            i32x2 hi, lo;
-            split_bf16x4(y, hi, lo);
-            const int64_t o = aoff(m, (int64_t)(t0 + wc * CW + tt) * 8 + h * 4, a.ld_act, a.o_mtiles);
-            *(i32x2*)(a.act + o) = hi;
-            *(i32x2*)(a.act_lo + o) = lo;
-          }
+        for (int i = 0; i < CWE; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (KS <= 4) {
+          add_slices(std::integral_constant<int, 4>{}, rt, 0, sum);
+        } else {
+          for (int z0 = 0; z0 < KS; z0 += NZ) add_slices(std::integral_constant<int, NZ>{}, rt, z0, sum);
         }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 16 * CPR / 64; ++j) {
-          const int idx = j * 64 + lane;
-          const int row = idx / CPR, pc = idx % CPR;
-          const int m = row0 + rl0 + row;
-          const int n = n_w0 + pc * 4;
-          const f32x4 y = *(const f32x4*)(stg + row * LDR + pc * 4);
-          if constexpr (EPI == EPI_SCALED_STORE) {
-            if (m < a.M) *(f32x4*)(a.out_f32 + (int64_t)m * a.ldo + n) = y * rinv_s[rl0 + row];
-          } else if constexpr (EPI == EPI_LOGITS_EB) {
-            if (m < a.M && a.out_f32 != nullptr) *(f32x4*)(a.out_f32 + (int64_t)m * a.ldo + n) = y * rinv_s[rl0 + row];
-          } else {  // EPI_RESID
-            float s2 = 0.f;
-            if (m < a.M) {
-              const f32x4 xv = xcur[j] + y;
-              *(f32x4*)(a.x + (int64_t)m * a.ldx + n) = xv;
-              f32x4 xg;
-              xg[0] = xv[0] * __uint_as_float((uint32_t)gw[0] << 16);
-              xg[1] = xv[1] * __uint_as_float((uint32_t)gw[0] & 0xffff0000u);
-              xg[2] = xv[2] * __uint_as_float((uint32_t)gw[1] << 16);
-              xg[3] = xv[3] * __uint_as_float((uint32_t)gw[1] & 0xffff0000u);
-              i32x2 hi, lo;
-              split_bf16x4(xg, hi, lo);
-              const int64_t on = aoff(m, n, a.ldx, a.o_mtiles);
-              *(i32x2*)(a.xn + on) = hi;
-              *(i32x2*)(a.xn_lo + on) = lo;
-              s2 = (xv[0] * xv[0] + xv[1] * xv[1]) + (xv[2] * xv[2] + xv[3] * xv[3]);
-            }
-#pragma unroll
-            for (int o = 1; o < CPR; o <<= 1) s2 += __shfl_xor(s2, o);  // the row's CPR lanes
-            if (pc == 0) ssq_s[wc][rl0 + row] = s2;
-          }
-        }
+        finish(rt, sum, xcur);
       }
-      if constexpr (EPI == EPI_LOGITS_EB) {
-        // the staged row tile again: lane L reduces VPL = 4 CW consecutive columns of row L / 4,
-        // 16 / CW lanes per 64-column chunk
-        constexpr int VPL = 4 * CW, LPC = 16 / CW;
-        static_assert(VPL * LPC == kEbFChunk, "a chunk is 64 columns");
-        const int row = lane >> 2, seg = lane & 3;
-        const int m = row0 + rl0 + row;
-        const int col0 = n_w0 + seg * VPL;
-        float mx;
-        int arg;
-        double z, sz;
-        eb_seg_stats<VPL, LPC>(stg + row * LDR + seg * VPL, rinv_s[rl0 + row], col0, a.eb_mask_id, mx, arg, z, sz);
-        if (seg % LPC == 0 && m < a.M) eb_chunk_store(a.eb_part, a.eb_arg, a.eb_chunks, m, col0 / kEbFChunk, mx, arg, z, sz);
+      if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int j = 0; j < NPASS; ++j) xcur[j] = xnxt[j];
       }
     }
-    if constexpr (EPI == EPI_RESID) {
+  } else {
 #pragma unroll
-      for (int j = 0; j < NPASS; ++j) xcur[j] = xnxt[j];
+    for (int mw = 0; mw < MTW; ++mw) {
+      if constexpr (EPI == EPI_RESID) {
+        if (mw + 1 < MTW) load_x(wm * MTW + mw + 1, xnxt);
+      }
+      if (cols_in) finish(wm * MTW + mw, acc[mw], xcur);
+      if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int j = 0; j < NPASS; ++j) xcur[j] = xnxt[j];
+      }
     }
   }
   if constexpr (EPI == EPI_RESID) {
@@ -557,7 +575,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs a) {
       const int m = row0 + threadIdx.x;
       float s = ssq_s[0][threadIdx.x];
 #pragma unroll
-      for (int q = 1; q < WC; ++q) s += ssq_s[q][threadIdx.x];
+      for (int q = 1; q < (kQuarter ? 4 : WC); ++q) s += ssq_s[q][threadIdx.x];
       if (m < a.M && own((int)threadIdx.x / 16)) a.sumsq_out[(int64_t)m * a.n_part_out + cb] = s;
     }
   }
@@ -610,51 +628,46 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
   return best;
 }
 
-template <int MT, int NT, int EPI>
+template <int MT, int NT, int EPI, bool W8>
 static void launch_cfg(const GemmArgs& a, const Exec& ex) {
   const int n_cb = (a.n_tiles + NT - 1) / NT;
   const unsigned grid = (unsigned)(((n_cb + 7) / 8) * 8 * a.splits * a.m_blocks);
-  const bool w8 = a.Wp8 != nullptr;
-  if constexpr (NT == 12) {  // bf16 weights only (gemm_plan)
-    if (a.m_blocks == 1)
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, true, false>), dim3(grid), dim3(256), ex, a);
-    else
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, false, false>), dim3(grid), dim3(256), ex, a);
-  } else {
-    if (a.m_blocks == 1 && w8)
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, true, true>), dim3(grid), dim3(256), ex, a);
-    else if (a.m_blocks == 1)
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, true, false>), dim3(grid), dim3(256), ex, a);
-    else if (w8)
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, false, true>), dim3(grid), dim3(256), ex, a);
-    else
-      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, false, false>), dim3(grid), dim3(256), ex, a);
+  if (a.splits > 1)
+    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true>), dim3(grid), dim3(512), ex, a);
+  else
+    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false>), dim3(grid), dim3(512), ex, a);
+}
+template <int MT, int NT, int EPI>
+static void launch_fmt(const GemmArgs& a, const Exec& ex) {
+  if constexpr (NT != 12) {  // 12-tile blocks: bf16 weights only (gemm_plan)
+    if (a.Wp8 != nullptr) return launch_cfg<MT, NT, EPI, true>(a, ex);
   }
+  launch_cfg<MT, NT, EPI, false>(a, ex);
 }
 
 template <int EPI>
 static void launch_epi(const GemmArgs& a, int mt, int nt, const Exec& ex) {
   if constexpr (EPI == EPI_SWIGLU) {
     if (nt == 12) {
-      if (mt == 2) launch_cfg<2, 12, EPI>(a, ex);
-      else if (mt == 4) launch_cfg<4, 12, EPI>(a, ex);
-      else launch_cfg<8, 12, EPI>(a, ex);
+      if (mt == 2) launch_fmt<2, 12, EPI>(a, ex);
+      else if (mt == 4) launch_fmt<4, 12, EPI>(a, ex);
+      else launch_fmt<8, 12, EPI>(a, ex);
       return;
     }
   }
   if (nt == 16) {
-    if (mt == 2) launch_cfg<2, 16, EPI>(a, ex);
-    else if (mt == 4) launch_cfg<4, 16, EPI>(a, ex);
-    else launch_cfg<8, 16, EPI>(a, ex);
+    if (mt == 2) launch_fmt<2, 16, EPI>(a, ex);
+    else if (mt == 4) launch_fmt<4, 16, EPI>(a, ex);
+    else launch_fmt<8, 16, EPI>(a, ex);
   } else {
-    if (mt == 2) launch_cfg<2, 8, EPI>(a, ex);
-    else if (mt == 4) launch_cfg<4, 8, EPI>(a, ex);
-    else launch_cfg<8, 8, EPI>(a, ex);
+    if (mt == 2) launch_fmt<2, 8, EPI>(a, ex);
+    else if (mt == 4) launch_fmt<4, 8, EPI>(a, ex);
+    else launch_fmt<8, 8, EPI>(a, ex);
   }
 }
 
 hipError_t launch_gemm(GemmEpi epi, const GemmArgs& a0, const Exec& ex) {
-  if (a0.M < 1 || a0.K < 32 || a0.K % 32 || a0.n_tiles < 8 || a0.n_tiles % 8) return hipErrorInvalidValue;
+  if (a0.M < 1 || a0.K < 32 || a0.K % 32 || a0.n_tiles < 8 || a0.n_tiles % 8 || a0.a_mtiles < 1) return hipErrorInvalidValue;
   if (a0.Wp8 != nullptr && a0.wscale == nullptr) return hipErrorInvalidValue;
   const bool nt12 = epi == EPI_SWIGLU && a0.Wp8 == nullptr;
   const bool half_block = (epi == EPI_SCALED_STORE || epi == EPI_LOGITS_EB) && a0.Wp8 == nullptr;

@@ -256,10 +256,10 @@ hipEvent_t take_event(sbd_ctx* c) {
 // K may be split over workgroups that hand their partials off through one XCD's L2, and
 // the slices of a unit may wait for each other, only when the device places workgroup i on
 // XCD i % 8 (probed at creation)
-GemmArgs gemm_base(const bf16_t* A, const bf16_t* A_lo, int64_t lda, int M, int K, const bf16_t* Wp,
+GemmArgs gemm_base(const bf16_t* A, const bf16_t* A_lo, int M, int K, const bf16_t* Wp,
                    int n_tiles, float* part, int64_t part_cap, int* counters, const sbd_ctx* c) {
   GemmArgs g{};
-  g.A = A; g.A_lo = A_lo; g.lda = lda; g.M = M; g.K = K; g.Wp = Wp; g.n_tiles = n_tiles;
+  g.A = A; g.A_lo = A_lo; g.M = M; g.K = K; g.Wp = Wp; g.n_tiles = n_tiles;
   g.part = part; g.part_cap = part_cap; g.counters = counters; g.no_split = c->xcd_ok ? 0 : 1;
   g.wait_ok = c->xcd_ok ? 1 : 0;
   g.spin_limit = c->wait_limit;
@@ -469,7 +469,7 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
       v.qkv = qe;
       SBD_LAUNCH(c, SBD_KERNEL_QKV, launch_gemv(EPI_QKV, v, GemvShape{}, ex));
     } else {
-      GemmArgs g = gemm_base(xn, xn_lo, d, M, d, wp, (int)(L.n_qkv / 16), vpart, vpart_cap, counters, c);
+      GemmArgs g = gemm_base(xn, xn_lo, M, d, wp, (int)(L.n_qkv / 16), vpart, vpart_cap, counters, c);
       g8((int64_t)l * L.wp_layer, (int64_t)l * L.ws_layer, g);
       g.a_mtiles = mt;
       g.out_f32 = qkv; g.ldo = L.n_qkv;
@@ -504,7 +504,7 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
       v.sumsq = sumsq; v.n_part = n_part_o;
       SBD_LAUNCH(c, SBD_KERNEL_O_PROJ, launch_gemv(EPI_RESID, v, GemvShape{}, ex));
     } else {
-      GemmArgs go = gemm_base(attn, attn_lo, qd, M, qd, wp + L.wp_o, d / 16, vpart, vpart_cap, counters, c);
+      GemmArgs go = gemm_base(attn, attn_lo, M, qd, wp + L.wp_o, d / 16, vpart, vpart_cap, counters, c);
       g8((int64_t)l * L.wp_layer + L.wp_o, (int64_t)l * L.ws_layer + L.ws_o, go);
       go.a_mtiles = mt; go.o_mtiles = mt;
       go.x = x; go.ldx = d; go.xn = xn; go.xn_lo = xn_lo; go.g_next = w.mlp_norm; go.sumsq_out = sumsq;
@@ -527,14 +527,14 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
       n_part_cur = n_part_down;
       SBD_LAUNCH(c, SBD_KERNEL_DOWN, launch_gemv(EPI_RESID, vd, GemvShape{}, ex));
     } else {
-      GemmArgs gu = gemm_base(xn, xn_lo, d, M, d, wp + L.wp_gu, m.ffn_dim / 8, vpart, vpart_cap, counters, c);
+      GemmArgs gu = gemm_base(xn, xn_lo, M, d, wp + L.wp_gu, m.ffn_dim / 8, vpart, vpart_cap, counters, c);
       g8((int64_t)l * L.wp_layer + L.wp_gu, (int64_t)l * L.ws_layer + L.ws_gu, gu);
       gu.a_mtiles = mt; gu.o_mtiles = mt;
       gu.sumsq_in = sumsq; gu.n_part = n_part_cur; gu.inv_d = 1.0f / d; gu.eps = m.rms_eps;
       gu.act = act; gu.act_lo = act_lo; gu.ld_act = m.ffn_dim;
       SBD_LAUNCH(c, SBD_KERNEL_GATE_UP, launch_gemm(EPI_SWIGLU, gu, ex));
 
-      GemmArgs gd = gemm_base(act, act_lo, m.ffn_dim, M, m.ffn_dim, wp + L.wp_down, d / 16, vpart, vpart_cap,
+      GemmArgs gd = gemm_base(act, act_lo, M, m.ffn_dim, wp + L.wp_down, d / 16, vpart, vpart_cap,
                               counters, c);
       g8((int64_t)l * L.wp_layer + L.wp_down, (int64_t)l * L.ws_layer + L.ws_down, gd);
       gd.a_mtiles = mt; gd.o_mtiles = mt;
@@ -561,7 +561,7 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
       SBD_LAUNCH(c, SBD_KERNEL_LM_HEAD, launch_gemv(lm_epi, v, GemvShape{}, ex));
     } else {
       // inputs in fragment order (also for one row of a prefill chunk: rows from a_row0)
-      GemmArgs gl = gemm_base(xn, xn_lo, d, Ml, d, c->at<bf16_t>(L.wpack) + L.wp_lm, m.vocab / 16, vpart,
+      GemmArgs gl = gemm_base(xn, xn_lo, Ml, d, c->at<bf16_t>(L.wpack) + L.wp_lm, m.vocab / 16, vpart,
                               vpart_cap, counters, c);
       g8(L.wp_lm, L.ws_lm, gl);
       gl.a_mtiles = mt; gl.a_row0 = r0;

@@ -113,12 +113,11 @@ struct QkvEpi {
 //
 // y[m][n] = sum_k A[m][k] * W[n][k] with W in the packed fragment order of gemm.hip.
 struct GemmArgs {
-  const bf16_t* A;     // hi part [M][K], row stride lda (a_mtiles == 0) or fragment order
+  const bf16_t* A;     // hi part [M][K], fragment order
   const bf16_t* A_lo;  // lo part, same layout
-  int64_t lda;
   int M, K;
-  int a_mtiles;        // A in fragment order with this many row tiles (0: row-major)
-  int a_row0;          // first row of A used (fragment order only)
+  int a_mtiles;        // row tiles of A's fragment order
+  int a_row0;          // first row of A used
   int o_mtiles;        // xn (EPI_RESID) and act (EPI_SWIGLU) written in fragment order (0: row-major)
   const bf16_t* Wp;    // packed weights
   const fp8_t* Wp8;    // or (non-null) e4m3 weights in the same packing, with per-row scales

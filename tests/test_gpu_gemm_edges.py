@@ -1,0 +1,58 @@
+"""The GEMM of more than 16 rows at the edges of its tiles, against the oracle.
+
+Row counts on both sides of its row blocks (32, 64, 128 rows, several blocks of 128) and
+ragged inside a 16-row tile, on a two-layer decoder whose projections split K 1 to 8 ways
+(d 1024: 32 K steps; ffn 2816: 88 steps, which 8 slices share unevenly) and whose vocabulary
+(136 tiles) ends in a half-full 16-tile block.  bf16 and e4m3 weights; logits, and the block
+step's statistics against the selection on the same logits.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import parity
+import synth
+from oracle import sbd_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = dataclasses.replace(synth.TINY_QK, name="edges", d_model=1024, n_q_heads=8, n_kv_heads=4, head_dim=128,
+                            ffn_dim=2816, vocab=2176, mask_id=2175)
+REGRESS = (5e-3, 6e-4)  # the bound of the synthetic-cache cases (about ten times the 8B layers' error)
+MAX_BATCH, MAX_BLOCK = 48, 16
+
+
+@pytest.fixture(scope="module", params=["bf16", "fp8"])
+def model(request):
+    from paper_2509_04185_amd import Sbd
+    make = synth.make_weights_fp8 if request.param == "fp8" else synth.make_weights
+    w = make(SHAPE, 9600, device="cuda")
+    lib = Sbd(SHAPE, w, max_batch=MAX_BATCH, max_seq_len=128, max_block=MAX_BLOCK)
+    host = O.Model(SHAPE, synth.weights_to_host(w), dtype=np.float64, kv_bf16=True)
+    caches = []
+    for b in range(MAX_BATCH):
+        kk, vv = synth.make_kv(SHAPE, 9600, b, 3 + (29 * b) % 71, device="cuda")
+        lib.kv_import(b, 0, kk, vv)
+        caches.append(O.SeqCache.from_arrays(synth.to_host_bits(kk), synth.to_host_bits(vv), np.float64))
+    yield lib, host, caches
+    lib.close()
+
+
+@pytest.mark.parametrize("B,k", [(17, 1), (4, 8), (11, 3), (4, 16), (5, 13), (16, 8), (43, 3), (25, 10), (17, 16), (43, 9)])
+def test_row_counts(model, B, k):
+    lib, host, caches = model
+    print(f"[gpu] GEMM edges: {B} x {k} = {B * k} rows, {lib.weight_format}", flush=True)
+    toks, is_mask = synth.block_rows(9610 + B, SHAPE, B, k, n_causal=1 if k > 1 else 0)
+    nc = [1 if k > 1 else 0] * B
+    got = lib.block_forward(list(range(B)), toks, is_mask=is_mask, n_causal=nc)
+    ref = host.block_forward(caches[:B], toks, nc).logits
+    parity.close(got.cpu().numpy(), ref, regress=REGRESS, label=f"{B}x{k}: ")
+    n, pos, tok, H, C, logits = lib.block_step(list(range(B)), toks, "eb_entropy", 20.0, is_mask=is_mask,
+                                               n_causal=nc, want_logits=True)
+    assert torch.equal(logits, got)
+    n2, pos2, tok2, H2, C2 = lib.select(got, is_mask, "eb_entropy", 20.0, SHAPE.mask_id)
+    on = torch.from_numpy(is_mask).bool().cuda()
+    assert (H[on] - H2[on]).abs().max() < 1e-10 and (C[on] - C2[on]).abs().max() < 1e-10
+    assert torch.equal(n, n2) and torch.equal(pos, pos2) and torch.equal(tok, tok2)
