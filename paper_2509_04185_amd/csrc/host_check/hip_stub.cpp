@@ -69,7 +69,7 @@ hipError_t launch_gemm(GemmEpi, const GemmArgs&, const Exec&) { return hipSucces
 GemvShape gemv_pick(GemmEpi, int, int) { return GemvShape{8, 1, 2, 1}; }
 hipError_t launch_gemv(GemmEpi, const GemvArgs&, GemvShape, const Exec&) { return hipSuccess; }
 hipError_t launch_pack(const bf16_t*, const bf16_t*, bf16_t*, int64_t, int, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_embed(const EmbedArgs&, const Exec&) { return hipSuccess; }
+hipError_t launch_embed(const EmbedArgs&, const InlineParams*, const Exec&) { return hipSuccess; }
 hipError_t launch_rope_stage(const RopeStageArgs&, const Exec&) { return hipSuccess; }
 hipError_t launch_rope_table(float*, int64_t, int, double, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_import(const KvCopyArgs&, hipStream_t) { return hipSuccess; }

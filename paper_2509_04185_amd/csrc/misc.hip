@@ -7,9 +7,13 @@
 //      with its positions permuted by vslot() so that one 16-byte load gives the eight
 //      values the attention kernel's P.V MFMA needs for one dimension.
 
+#include <type_traits>
+
 #include "sbd_device.h"
 
 namespace sbd {
+
+struct NoInline {};  // embed_kernel without inline parameters
 
 // Storage slot inside a 32-position V block of position p (0..31): positions
 // {16t + 4q + i : t in {0,1}, i < 4} (the keys lane group q holds after the score MFMA)
@@ -24,11 +28,26 @@ __device__ __forceinline__ int64_t kv_head_base(int layer, int slot, int g, int 
 // Row m = blockIdx.x, columns 1024 blockIdx.y + 4 t .. + 3 for thread t (every load of a
 // thread is issued at once): x[m] = E[tok[m]] (fp32), xn[m] = x * g as hi/lo bf16,
 // sumsq[m][c/16] = sum over each 16 columns of x^2 (the consumer forms 1/rms).
-__global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
+// With inline parameters (INL is InlineParams) the token comes from the kernel's arguments and
+// the first workgroup writes the parameters where the kernels that follow read them: two
+// host-to-device copies of a few hundred bytes in front of every forward, each a dispatch of
+// its own and a pinned slot to wait for, cost 14 us of a call (tiny decoder, 4 rows: 91.7 -> 77.5 us).
+template <class INL>
+__global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a, INL inl) {
+  constexpr bool kInline = std::is_same<INL, InlineParams>::value;
   const int m = blockIdx.x;
+  if constexpr (kInline) {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+      const int t = threadIdx.x;
+      if (t < a.M) a.rows_out[t] = inl.rows[t];  // M <= kInlineRows = the workgroup's threads
+      if (t < a.B) a.seqs_out[t] = inl.seqs[t];
+    }
+  }
   const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (c >= a.d) return;  // d % 16 == 0: a 16-column group lies inside or outside as a whole
-  const int tok = a.rows[m].tok;
+  int tok;
+  if constexpr (kInline) tok = inl.rows[m].tok;
+  else tok = a.rows[m].tok;
   const uint2 ev = *reinterpret_cast<const uint2*>(a.embed + (int64_t)tok * a.d + c);
   const uint2 gv = *reinterpret_cast<const uint2*>(a.g + c);
   const float v[4] = {__uint_as_float(ev.x << 16), __uint_as_float(ev.x & 0xffff0000u),
@@ -58,9 +77,16 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
   if ((threadIdx.x & 3) == 0) a.sumsq[(int64_t)m * (a.d / 16) + c / 16] = s;
 }
 
-hipError_t launch_embed(const EmbedArgs& a, const Exec& ex) {
+hipError_t launch_embed(const EmbedArgs& a, const InlineParams* inl, const Exec& ex) {
   if (a.d % 16 != 0) return hipErrorInvalidValue;
-  SBD_KLAUNCH(embed_kernel, dim3(a.M, (a.d + 1023) / 1024), dim3(256), ex, a);
+  const dim3 grid(a.M, (a.d + 1023) / 1024);
+  if (inl != nullptr) {
+    if (a.M > kInlineRows || a.B > kInlineSeqs || a.rows_out == nullptr || a.seqs_out == nullptr)
+      return hipErrorInvalidValue;
+    SBD_KLAUNCH(embed_kernel<InlineParams>, grid, dim3(256), ex, a, *inl);
+  } else {
+    SBD_KLAUNCH(embed_kernel<NoInline>, grid, dim3(256), ex, a, NoInline{});
+  }
   return hipGetLastError();
 }
 

@@ -385,16 +385,23 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
     return fail(c, SBD_ERR_UNSUPPORTED, "the per-XCD layer kernels do not fit this forward or device (%d CUs%s)",
                 c->n_cu_dev, c->xcd_ok ? "" : "; workgroup i does not run on XCD i % 8 here");
 
-  sbd_status st = upload(c, c->ws + L.rows, rows.data(), rows.size() * sizeof(RowParam));
-  if (st) return st;
-  st = upload(c, c->ws + L.seqs, seqs.data(), seqs.size() * sizeof(SeqParam));
-  if (st) return st;
+  // the forward's parameters: in the embedding kernel's arguments where they fit, else uploaded
+  const bool inl = M <= kInlineRows && B <= kInlineSeqs;
+  InlineParams ip;
+  if (inl) {
+    std::copy(rows.begin(), rows.end(), ip.rows);
+    std::copy(seqs.begin(), seqs.end(), ip.seqs);
+  } else {
+    if (sbd_status st = upload(c, c->ws + L.rows, rows.data(), rows.size() * sizeof(RowParam))) return st;
+    if (sbd_status st = upload(c, c->ws + L.seqs, seqs.data(), seqs.size() * sizeof(SeqParam))) return st;
+  }
   // the per-XCD layer kernels' residual buffers R0, R1, R2 (kLxMaxRows rows each)
   int64_t* xr[3];
   for (int i = 0; i < 3; ++i) xr[i] = c->at<int64_t>(L.x64) + (int64_t)i * kLxMaxRows * d;
   EmbedArgs ea{drows, M, d, c->embed, c->layers[0].attn_norm, x, xn, xn_lo, sumsq, mt,
-               layers_fit ? xr[0] : nullptr, layers_fit ? xr[1] : nullptr};
-  SBD_LAUNCH(c, SBD_KERNEL_EMBED, launch_embed(ea, ex));
+               layers_fit ? xr[0] : nullptr, layers_fit ? xr[1] : nullptr,
+               c->at<RowParam>(L.rows), c->at<SeqParam>(L.seqs), B};
+  SBD_LAUNCH(c, SBD_KERNEL_EMBED, launch_embed(ea, inl ? &ip : nullptr, ex));
   if (fused) {
     SBD_HIP(c, hipMemsetAsync(f.ctl, 0, (size_t)f.plan.n_ctl * sizeof(int32_t), c->stream));
     SBD_LAUNCH(c, SBD_KERNEL_FUSED, launch_fused_forward(f, c->n_cu, ex));

@@ -47,7 +47,7 @@ struct SeqParam {
 // Where each buffer lives inside the caller's workspace (byte offsets).
 struct Layout {
   int64_t cap;            // cache capacity per slot (max_seq_len rounded up to 64)
-  int64_t m_max;          // rows per forward (max(max_batch*max_block, prefill_chunk))
+  int64_t m_max;          // rows per forward (max(max_batch*max_block, prefill chunk))
   int64_t n_qkv;          // (n_q_heads + 2 n_kv_heads) * head_dim
   int64_t n_part;         // d_model / 16 sum-of-squares partials per row
   int64_t eb_chunks;      // ceil(vocab / kEbChunk)
@@ -232,6 +232,15 @@ hipError_t launch_pack(const bf16_t* src0, const bf16_t* src1, bf16_t* dst, int6
                        int mode, hipStream_t s);
 
 // ---------------------------------------------------------------------------- misc kernels
+// Parameters of a forward of at most kInlineRows rows and kInlineSeqs sequences travel in the
+// embedding kernel's arguments (3 KB of the 4 KB a launch takes).
+constexpr int kInlineRows = 256;
+constexpr int kInlineSeqs = 64;
+struct InlineParams {
+  RowParam rows[kInlineRows];
+  SeqParam seqs[kInlineSeqs];
+};
+
 struct EmbedArgs {
   const RowParam* rows;
   int M, d;
@@ -244,8 +253,14 @@ struct EmbedArgs {
   int mtiles;    // xn, xn_lo in fragment order with this many row tiles (0: row-major)
   int64_t* x64;       // the same rows as fixed point (x * 2^32) for the per-XCD layer kernels, or null
   int64_t* x64_zero;  // with x64: the buffer the first layer kernel adds into, zeroed here
+  // with inline parameters: where the rows (M) and sequences (B) go for the kernels that follow
+  RowParam* rows_out;
+  SeqParam* seqs_out;
+  int B;
 };
-hipError_t launch_embed(const EmbedArgs& a, const Exec& ex);
+// inl: the forward's parameters by value (M <= kInlineRows, B <= kInlineSeqs), or null: a.rows
+// holds them on the device already.
+hipError_t launch_embed(const EmbedArgs& a, const InlineParams* inl, const Exec& ex);
 
 struct RopeStageArgs {
   const RowParam* rows;
