@@ -57,7 +57,8 @@ enum { SBD_SELECT_EB_ENTROPY = 0, SBD_SELECT_EB_CONFIDENCE = 1, SBD_SELECT_FACTO
  *   max_batch: number of sequence slots (ids 0..max_batch-1).
  *   max_seq_len: tokens per slot, including the k rows staged by a block forward.
  *   max_block: largest k accepted by sbd_block_forward / sbd_eb_select (<= 64).
- *   prefill_chunk: rows per forward inside sbd_prefill (0 selects 256).
+ *   prefill_chunk: rows per forward inside sbd_prefill at most (0: the library chooses, up to
+ *   1024).
  */
 typedef struct {
   int32_t n_layers, d_model, n_q_heads, n_kv_heads, head_dim, ffn_dim, vocab, mask_id;

@@ -153,12 +153,22 @@ __device__ __forceinline__ void slices_arrived(const GemmArgs& a, int* ctr, int 
   __syncthreads();
 }
 
+// FOLD: every K step's products of a tile (hi and lo, two MFMAs from zero) are added to its sum
+// with ordinary fp32 additions, instead of 2 K / 32 MFMAs accumulating in a row.  The MFMA does
+// not round its sum to nearest, and the error of such a chain grows with its length: the keys
+// and values of an unsplit QKV projection (K = 4096, 256 MFMAs in a row) round to another bf16
+// than the exact ones 1.6 times as often as with five K slices (Qwen 8B prefill of 2048, four
+// layers, against float64: keys 5.8e-4 unsplit, 4.6e-4 in slices, 4.4e-4 with FOLD; logits
+// 1.5e-4, 0.91e-4, 0.91e-4), while the other projections' chains make no difference (logits
+// 0.91e-4 with or without).  It costs two additions per MFMA, 17 % of the kernel at 1024 rows
+// (QKV of Llama 8B 91 -> 107 us in 16-tile blocks), so only the QKV projection of prefill
+// chunks of more than 256 rows, which need no K slices to fill the chip, takes it.
 // SPLIT: K is split over a.splits workgroups (kernels of their own: without the other case's
 // epilogue the accumulators are dead once parked, and the slices' sums get their registers).
 // W8: the weights are e4m3 bytes (a.Wp8, per-row scales a.wscale) in the same packing, one
 // byte per element; a fragment is widened to the bf16 MFMA operand (times its row's scale,
 // exact) after its LDS read, so the products are those of the widened bf16 matrix.
-template <int MT, int NT, int EPI, bool W8, bool SPLIT>
+template <int MT, int NT, int EPI, bool W8, bool SPLIT, bool FOLD>
 __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   using Cfg = MidCfg<MT, NT, W8>;
   constexpr int WC = Cfg::WC, CW = Cfg::CW, MTW = Cfg::MTW, NS = Cfg::NS, FPW = Cfg::FPW;
@@ -334,6 +344,16 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   constexpr int WPM = (CW + MTW - 1) / MTW;  // weight reads per row tile
   // step cc: MFMAs of stage cc; every accumulator takes hi, then lo (e4m3 fragments are
   // widened once per row tile).  P0: parity of the register pair holding row tile 0.
+  f32x4 fold[2][2];                  // FOLD: a step's products of two pairs of tiles
+  float facc[FOLD ? MTW : 1][CW][4];  // and the sums (single floats: as vectors they spill)
+#pragma unroll
+  for (int mw = 0; mw < (FOLD ? MTW : 1); ++mw)
+#pragma unroll
+    for (int cw = 0; cw < CW; ++cw)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) facc[mw][cw][e] = 0.f;
+  i32x4 wide[W8 ? CW : 1];           // e4m3: the step's widened fragments (FOLD), or one
+  if constexpr (FOLD) fold[1][0] = fold[1][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto step = [&](auto P0, int cc, WFr (&wc_)[CW], WFr (&wn)[CW]) {
     if (cc + 1 < nst) bar();
     const int nslot = rslot + STAGE == NS * STAGE ? 0 : rslot + STAGE;
@@ -343,7 +363,6 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
       constexpr int wleft = CW - mw * WPM, nw = wleft < 0 ? 0 : (wleft < WPM ? wleft : WPM);  // weight reads here
       constexpr bool kNext = mw + 1 == MTW;
       constexpr int NM = 2 * CW;
-      i32x4 wide;
       static_for<NM>([&](auto I) {
         constexpr int i = decltype(I)::value;
         // reads: the next row tile's hi and lo, then this row tile's share of the next stage's weights
@@ -355,10 +374,24 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
           else wn[x] = ds_read16<x * 1024>(lds_w + nslot);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (W8) {
+        if constexpr (FOLD) {
+          // tiles in pairs: lo, lo, hi, hi into fresh registers; meanwhile the pair before is
+          // added (the pairs of a step alternate between two register sets: pn is even)
+          constexpr int pn = mw * (CW / 2) + i / 4, cw = (i / 4) * 2 + i % 2, h = 1 - (i % 4) / 2, par = pn & 1;
+          constexpr int pv = (pn + MTW * CW / 2 - 1) % (MTW * CW / 2), pmw = pv / (CW / 2), pcw = (pv % (CW / 2)) * 2;
+          if constexpr (W8) {
+            if constexpr (mw == 0 && h == 1) wide[cw] = e4m3x8_to_bf16(wc_[cw], wsc[cw]);
+            fold[par][i % 2] = mfma16x16x32(av[p][h], wide[cw], h ? f32x4{0.f, 0.f, 0.f, 0.f} : fold[par][i % 2]);
+          } else {
+            fold[par][i % 2] = mfma16x16x32(av[p][h], wc_[cw], h ? f32x4{0.f, 0.f, 0.f, 0.f} : fold[par][i % 2]);
+          }
+          constexpr int e0 = (i % 2) * 2, ft = (i % 4) / 2;  // two of the eight additions
+          facc[pmw][pcw + ft][e0] += fold[par ^ 1][ft][e0];
+          facc[pmw][pcw + ft][e0 + 1] += fold[par ^ 1][ft][e0 + 1];
+        } else if constexpr (W8) {
           constexpr int cw = i / 2, h = i % 2;
-          if constexpr (h == 0) wide = e4m3x8_to_bf16(wc_[cw], wsc[cw]);
-          acc[mw][cw] = mfma16x16x32(av[p][h], wide, acc[mw][cw]);
+          if constexpr (h == 0) wide[0] = e4m3x8_to_bf16(wc_[cw], wsc[cw]);
+          acc[mw][cw] = mfma16x16x32(av[p][h], wide[0], acc[mw][cw]);
         } else {
           constexpr int h = i / CW, cw = i % CW;
           acc[mw][cw] = mfma16x16x32(av[p][h], wc_[cw], acc[mw][cw]);
@@ -381,6 +414,18 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   for (int c = 0; c < nst; c += 2) {
     step(std::integral_constant<int, 0>{}, c, wv0, wv1);
     if (c + 1 < nst) step(std::integral_constant<int, MTW & 1>{}, c + 1, wv1, wv0);
+  }
+
+  if constexpr (FOLD) {  // the last step's last pair
+    static_assert(MTW * CW % 4 == 0, "an even number of pairs per step");
+#pragma unroll
+    for (int mw = 0; mw < MTW; ++mw)
+#pragma unroll
+      for (int cw = 0; cw < CW; ++cw)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[mw][cw][e] = facc[mw][cw][e];
+    acc[MTW - 1][CW - 2] += fold[1][0];
+    acc[MTW - 1][CW - 1] += fold[1][1];
   }
 
   // ---- K split over workgroups (a plan of one round: every slice of a unit is resident):
@@ -589,8 +634,9 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
   const int mb = (M + mt * 16 - 1) / (mt * 16);
   const int S_all = K / 32;
   double best_cost = 1e300;
-  // 12-tile blocks (gate/up only): Qwen 8B's 1536 gate/up tiles then fill all 32 CUs of an
-  // XCD in one round (16 blocks x 2 K slices) where 16-tile blocks leave 8 idle
+  // 12-tile blocks (gate/up, and the QKV projection of prefill chunks): Qwen 8B's 1536 gate/up tiles then fill all 32 CUs of an
+  // XCD in one round (16 blocks x 2 K slices) where 16-tile blocks leave 8 idle, and so do the
+  // 384 tiles of QKV at 1024 rows (32 blocks x 8 row blocks against 24 x 8)
   for (int nt : {16, 12, 8}) {
     // half_block: 16-tile blocks also when n_tiles % 16 == 8, the last one half full (one K
     // slice: its empty half would otherwise park and sum nothing)
@@ -632,10 +678,19 @@ template <int MT, int NT, int EPI, bool W8>
 static void launch_cfg(const GemmArgs& a, const Exec& ex) {
   const int n_cb = (a.n_tiles + NT - 1) / NT;
   const unsigned grid = (unsigned)(((n_cb + 7) / 8) * 8 * a.splits * a.m_blocks);
+  if constexpr (MT == 8 && EPI == EPI_SCALED_STORE) {
+    if (a.fold) {
+      if (a.splits > 1)
+        SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true, true>), dim3(grid), dim3(512), ex, a);
+      else
+        SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false, true>), dim3(grid), dim3(512), ex, a);
+      return;
+    }
+  }
   if (a.splits > 1)
-    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true>), dim3(grid), dim3(512), ex, a);
+    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true, false>), dim3(grid), dim3(512), ex, a);
   else
-    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false>), dim3(grid), dim3(512), ex, a);
+    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false, false>), dim3(grid), dim3(512), ex, a);
 }
 template <int MT, int NT, int EPI>
 static void launch_fmt(const GemmArgs& a, const Exec& ex) {
@@ -643,6 +698,14 @@ static void launch_fmt(const GemmArgs& a, const Exec& ex) {
     if (a.Wp8 != nullptr) return launch_cfg<MT, NT, EPI, true>(a, ex);
   }
   launch_cfg<MT, NT, EPI, false>(a, ex);
+}
+
+static void launch_fold12(const GemmArgs& a, const Exec& ex) {
+  const unsigned grid = (unsigned)(((a.n_tiles / 12 + 7) / 8) * 8 * a.splits * a.m_blocks);
+  if (a.splits > 1)
+    SBD_KLAUNCH((gemm_kernel<8, 12, EPI_SCALED_STORE, false, true, true>), dim3(grid), dim3(512), ex, a);
+  else
+    SBD_KLAUNCH((gemm_kernel<8, 12, EPI_SCALED_STORE, false, false, true>), dim3(grid), dim3(512), ex, a);
 }
 
 template <int EPI>
@@ -654,6 +717,9 @@ static void launch_epi(const GemmArgs& a, int mt, int nt, const Exec& ex) {
       else launch_fmt<8, 12, EPI>(a, ex);
       return;
     }
+  }
+  if constexpr (EPI == EPI_SCALED_STORE) {
+    if (nt == 12) return launch_fold12(a, ex);  // with FOLD only: eight row tiles (launch_gemm)
   }
   if (nt == 16) {
     if (mt == 2) launch_fmt<2, 16, EPI>(a, ex);
@@ -669,7 +735,8 @@ static void launch_epi(const GemmArgs& a, int mt, int nt, const Exec& ex) {
 hipError_t launch_gemm(GemmEpi epi, const GemmArgs& a0, const Exec& ex) {
   if (a0.M < 1 || a0.K < 32 || a0.K % 32 || a0.n_tiles < 8 || a0.n_tiles % 8 || a0.a_mtiles < 1) return hipErrorInvalidValue;
   if (a0.Wp8 != nullptr && a0.wscale == nullptr) return hipErrorInvalidValue;
-  const bool nt12 = epi == EPI_SWIGLU && a0.Wp8 == nullptr;
+  if (a0.fold && (epi != EPI_SCALED_STORE || a0.M <= 64)) return hipErrorInvalidValue;  // row blocks of eight tiles
+  const bool nt12 = (epi == EPI_SWIGLU || (epi == EPI_SCALED_STORE && a0.fold)) && a0.Wp8 == nullptr;
   const bool half_block = (epi == EPI_SCALED_STORE || epi == EPI_LOGITS_EB) && a0.Wp8 == nullptr;
   const GemmPlan p = gemm_plan(a0.M, a0.n_tiles, a0.K, (a0.part && !a0.no_split) ? a0.part_cap : 0, nt12, half_block);
   if (p.nt == 0) return hipErrorInvalidValue;

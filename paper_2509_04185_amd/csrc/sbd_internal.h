@@ -15,6 +15,8 @@ typedef uint8_t fp8_t;              // raw OCP e4m3 (fn) bits
 
 constexpr int kWave = 64;           // CDNA wavefront width
 constexpr int kMaxSplits = 64;      // split-KV partitions per (sequence, KV head, row block)
+constexpr int kAttnCus = 256;       // CUs the attention's key splits are sized for at most
+constexpr int kPrefillRows = 1024;  // rows per prefill forward when the configuration names none
 constexpr int kEbChunk = 4096;      // vocabulary entries per EB partial workgroup
 constexpr int kEbInlineRows = 2048;  // masks of at most this many rows are passed by value
 constexpr int kMaxBlock = 64;       // largest block size k
@@ -58,6 +60,7 @@ struct Layout {
   int64_t ws_layer, ws_o, ws_gu, ws_down, ws_lm;
   int64_t wp_layer;          // elements per layer: qkv, then o, then gate/up, then down
   int64_t wp_o, wp_gu, wp_down, wp_lm;
+  int64_t attn_items;        // (split, row, query head) partials of the attention at most
   size_t attn_ml, attn_o, rows, seqs, eb_mask, eb_part, eb_arg, gemv_part, counters;
   // sbd_block_step: the LM head's 64-column chunk statistics and the merged row values
   size_t eb_fpart, eb_farg, eb_rowstat, eb_rowtok;
@@ -165,6 +168,7 @@ struct GemmArgs {
   // set by launch_gemm from the plan
   int splits, m_blocks;
   int no_split;        // 1: one K slice per unit (no hand-off between workgroups)
+  int fold;            // 1: every K step's products added in fp32 (EPI_SCALED_STORE, M > 64)
 };
 
 // How launch_gemm cuts a product: mt 16-row tiles per row block (m_blocks row blocks),
@@ -172,8 +176,8 @@ struct GemmArgs {
 struct GemmPlan {
   int mt, nt, splits, m_blocks, n_cb;
 };
-// nt12: 12-tile column blocks may be used (EPI_SWIGLU with bf16 weights: an epilogue
-// without row reductions across the block's columns).  half_block: 16-tile blocks may be
+// nt12: 12-tile column blocks may be used (EPI_SWIGLU and folding EPI_SCALED_STORE with bf16
+// weights: epilogues without row reductions across the block's columns).  half_block: 16-tile blocks may be
 // used when n_tiles % 16 == 8, the last one half full (EPI_SCALED_STORE / EPI_LOGITS_EB with
 // bf16 weights; n_cb then counts it).
 GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12 = false, bool half_block = false);
