@@ -179,6 +179,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
   __shared__ float rinv_s[MT * 16];
   __shared__ float ssq_s[4][MT * 16];
+  __shared__ double exp_tab[EPI == EPI_LOGITS_EB ? 32 : 1];
 
   const int lane = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), w = w8 & 3;
   const int r = lane & 15, g = lane >> 4;
@@ -447,6 +448,8 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
     load_x(wm * MTW, xcur);
   }
 
+  if constexpr (EPI == EPI_LOGITS_EB) exp_table_stage(exp_tab, threadIdx.x);  // read past the barrier below
+
   // ---- 1/rms of the block's rows (partials beyond the prefetched ones read here)
   if constexpr (EPI != EPI_RESID) {
     float sq = 0.f;
@@ -552,7 +555,8 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
       float mx;
       int arg;
       double z, sz;
-      eb_seg_stats<VPL, LPC>(stg + row * LDR + seg * VPL, rinv_s[rl0 + row], col0, a.eb_mask_id, mx, arg, z, sz);
+      eb_seg_stats<VPL, LPC>(stg + row * LDR + seg * VPL, rinv_s[rl0 + row], col0, a.eb_mask_id, exp_tab, mx,
+                             arg, z, sz);
       if (seg % LPC == 0 && m < a.M) eb_chunk_store(a.eb_part, a.eb_arg, a.eb_chunks, m, col0 / kEbFChunk, mx, arg, z, sz);
     }
   };

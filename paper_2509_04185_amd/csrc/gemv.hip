@@ -197,6 +197,8 @@ __global__ __launch_bounds__(NW * 64) void gemv_kernel(GemvArgs a) {
     // columns]; then lane L reduces 32 columns of row L / 4 (quarter L % 4), two lanes per
     // 64-column chunk
     __shared__ __attribute__((aligned(16))) float st[16][8 * 16 + 4];
+    __shared__ double exp_tab[32];
+    exp_table_stage(exp_tab, lane);
 #pragma unroll
     for (int ct = 0; ct < C; ++ct)
 #pragma unroll
@@ -210,7 +212,8 @@ __global__ __launch_bounds__(NW * 64) void gemv_kernel(GemvArgs a) {
     float mx;
     int arg;
     double z, sz;
-    eb_seg_stats<32, 2>(&st[row][seg * 32], a.sumsq_in != nullptr ? rinv_s[row] : 1.f, t0 * 16 + seg * 32, a.eb_mask_id, mx, arg, z, sz);
+    eb_seg_stats<32, 2>(&st[row][seg * 32], a.sumsq_in != nullptr ? rinv_s[row] : 1.f, t0 * 16 + seg * 32, a.eb_mask_id,
+                        exp_tab, mx, arg, z, sz);
     if ((seg & 1) == 0 && row < a.M) eb_chunk_store(a.eb_part, a.eb_arg, a.eb_chunks, row, t0 / 4 + seg / 2, mx, arg, z, sz);
     return;
   } else {
