@@ -14,7 +14,7 @@
 // gemv.hip.  At these M every projection still reads far more weight bytes than it does
 // MFMA work per byte (M flop per weight byte, against a ridge of ~300), so the design
 // streams every weight byte from HBM once:
-//   - A workgroup owns a column block of NT tiles (128, 256, or for gate/up 192 columns) and a row block of
+//   - A workgroup owns a column block of NT tiles (8, 12, 14 or 16: gemm_plan) and a row block of
 //     MT tiles (up to 128 rows; larger M is cut into row blocks that run on the same XCD
 //     and meet the same weights in its L2), and a range of K steps.
 //   - Eight waves: four load, four multiply, one of each on a SIMD.  The loading waves bring
@@ -73,11 +73,11 @@ struct MidCfg {
   // carries two tiles' fragments)
   static constexpr int WB = NT * (W8 ? 512 : 1024);
   static constexpr int NWL = WB / 1024;               // weight wave-loads per stage
-  static constexpr int STAGE = WB + 2 * MT * 1024;    // one K step: weights + 2 MT A fragments
+  static constexpr int NWU = (NWL + 3) / 4;           // of each loading wave (past the last: read again)
+  static constexpr int STAGE = NWU * 4096 + 2 * MT * 1024;  // one K step: weights + 2 MT A fragments
   static constexpr int NS = (144 * 1024) / STAGE > 8 ? 8 : (144 * 1024) / STAGE;  // ring stages
-  static constexpr int FPW = (NWL + 2 * MT) / 4;      // wave-loads of each loading wave per stage
-  static constexpr int NWU = NWL / 4;                 // of a wave's FPW loads, the first NWU are weights
-  static_assert(MTW >= 1 && (NWL + 2 * MT) % 4 == 0 && NWL % 4 == 0, "unsupported tile shape");
+  static constexpr int FPW = NWU + MT / 2;            // wave-loads of each loading wave per stage, weights first
+  static_assert(MTW >= 1 && MT % 2 == 0 && CW * WC == NT, "unsupported tile shape");
   static_assert(NS >= 3 && (NS - 1) * FPW <= 63, "vmcnt range");
 };
 
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   using Cfg = MidCfg<MT, NT, W8>;
   constexpr int WC = Cfg::WC, CW = Cfg::CW, MTW = Cfg::MTW, NS = Cfg::NS, FPW = Cfg::FPW;
   constexpr int STAGE = Cfg::STAGE;
-  constexpr int WB = Cfg::WB;    // weight bytes of a stage; A fragments follow
+  constexpr int WB = Cfg::NWU * 4096;  // weight bytes of a stage; A fragments follow
   constexpr int NWU = Cfg::NWU;
   typedef typename std::conditional<W8, i32x2, i32x4>::type WFr;  // a weight fragment in registers
   __shared__ __attribute__((aligned(16))) char smem[NS * STAGE];
@@ -208,9 +208,10 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
     asm volatile("" ::: "memory");
   };
   if (w8 >= 4) {
-    // ---- loading wave: load u of a stage fills 1 KB f = w + 4u of it; f < NWL is weight tile
+    // ---- loading wave: load u of a stage fills 1 KB f = w + 4u of it; for u < NWU weight tile
     // t0 + f (bf16) or the tiles t0 + 2f, t0 + 2f + 1 (e4m3: their fragments are adjacent in
-    // the packing), else A fragment f - NWL = 2 * (row tile) + (0: hi, 1: lo).
+    // the packing; f past the last re-reads it), else A fragment f - 4 NWU = 2 * (row tile) +
+    // (0: hi, 1: lo).
     constexpr int64_t kWStep = W8 ? kPackStep : kPackStep * 2;
     const char* src[FPW];
     const int64_t a_step = (int64_t)a.a_mtiles * 1024;
@@ -219,14 +220,15 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
       const int f = w + 4 * u;
       if (u < NWU) {
         if constexpr (W8) {
-          src[u] = (const char*)(a.Wp8 + packed_frag(t0 + 2 * f, s_b, S_all)) + lane * 16;
+          src[u] = (const char*)(a.Wp8 + packed_frag(t0 + 2 * min(f, Cfg::NWL - 1), s_b, S_all)) + lane * 16;
         } else {
           // a half-full block's tiles past the end read the last tile (results discarded)
           constexpr bool kHalf = EPI == EPI_SCALED_STORE || EPI == EPI_LOGITS_EB;
-          src[u] = (const char*)(a.Wp + packed_frag(kHalf ? min(t0 + f, a.n_tiles - 1) : t0 + f, s_b, S_all)) + lane * 16;
+          const int t = t0 + min(f, Cfg::NWL - 1);
+          src[u] = (const char*)(a.Wp + packed_frag(kHalf ? min(t, a.n_tiles - 1) : t, s_b, S_all)) + lane * 16;
         }
       } else {
-        const int ai = f - Cfg::NWL;
+        const int ai = f - 4 * NWU;
         const int row = min(row0 + (ai >> 1) * 16 + r, a.M - 1);  // rows past the end: valid data, results discarded
         src[u] = (const char*)(((ai & 1) ? a.A_lo : a.A) + apack(a.a_row0 + row, (int64_t)s_b * 32 + g * 8, a.a_mtiles));
       }
@@ -303,8 +305,9 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
 
   // The epilogue's share of a wave.  One slice: the wave's own accumulators, CW tiles of MTW
   // row tiles.  Split: a quarter of the columns of each of the slice's row tiles (a half of
-  // every second one for EB statistics, whose 64-column chunks stay inside one wave).
-  constexpr bool kQuarter = SPLIT && EPI != EPI_LOGITS_EB;
+  // every second one for EB statistics, whose 64-column chunks stay inside one wave, and for
+  // blocks of 14 tiles).
+  constexpr bool kQuarter = SPLIT && EPI != EPI_LOGITS_EB && NT % 4 == 0;
   constexpr int CWE = kQuarter ? NT / 4 : CW;   // tiles of a row tile
   constexpr int CPR = CWE * 4;                  // float4 pieces of a row
   constexpr int NPASS = 16 * CPR / 64;          // read-back passes per row tile
@@ -583,7 +586,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
           for (int i = 0; i < CWE; ++i) sum[i] += __builtin_bit_cast(f32x4, v[zz][i]);
         }
     };
-    constexpr int NZ = CWE >= 8 ? 4 : 8;
+    constexpr int NZ = CWE >= 7 ? 4 : 8;
 #pragma unroll 1
     for (int rt = kc; rt < MT; rt += KS) {
       if constexpr (EPI == EPI_RESID) {
@@ -632,7 +635,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
 
 // ---- host side: plan and launch
 
-GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool half_block) {
+GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool half_block, bool nt14) {
   GemmPlan best{};
   const int mt = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
   const int mb = (M + mt * 16 - 1) / (mt * 16);
@@ -640,12 +643,17 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
   double best_cost = 1e300;
   // 12-tile blocks (gate/up, and the QKV projection of prefill chunks): Qwen 8B's 1536 gate/up tiles then fill all 32 CUs of an
   // XCD in one round (16 blocks x 2 K slices) where 16-tile blocks leave 8 idle, and so do the
-  // 384 tiles of QKV at 1024 rows (32 blocks x 8 row blocks against 24 x 8)
-  for (int nt : {16, 12, 8}) {
+  // 384 tiles of QKV at 1024 rows (32 blocks x 8 row blocks against 24 x 8).  14-tile blocks
+  // (gate/up of more than 64 rows): Llama 8B's 1792 tiles are 128 of them, 256 workgroups at
+  // 256 rows where 16-tile blocks leave 32 CUs idle; gate/up at 1024 rows 367 -> 353 us, at 256
+  // rows 99.9 -> 97.0, with e4m3 weights at 128 rows 62.8 -> 60.1.  With fewer rows the stream
+  // of the weights sets the time and the split they need costs more than they gain (64 rows
+  // 48.8 -> 53.0 us, 32 rows 39.9 -> 43.7).
+  for (int nt : {16, 14, 12, 8}) {
     // half_block: 16-tile blocks also when n_tiles % 16 == 8, the last one half full (one K
     // slice: its empty half would otherwise park and sum nothing)
     const bool half = half_block && nt == 16 && n_tiles % 16 == 8;
-    if ((n_tiles % nt && !half) || (nt == 12 && !nt12)) continue;
+    if ((n_tiles % nt && !half) || (nt == 12 && !nt12) || (nt == 14 && (!nt14 || mt < 8))) continue;
     const int n_cb = (n_tiles + nt - 1) / nt;
     for (int ks = 1; ks <= 8; ++ks) {
       if (ks > 1 && (S_all / ks < 4 || half)) break;
@@ -715,6 +723,7 @@ static void launch_fold12(const GemmArgs& a, const Exec& ex) {
 template <int EPI>
 static void launch_epi(const GemmArgs& a, int mt, int nt, const Exec& ex) {
   if constexpr (EPI == EPI_SWIGLU) {
+    if (nt == 14) return launch_fmt<8, 14, EPI>(a, ex);  // eight row tiles only (gemm_plan)
     if (nt == 12) {
       if (mt == 2) launch_fmt<2, 12, EPI>(a, ex);
       else if (mt == 4) launch_fmt<4, 12, EPI>(a, ex);
@@ -742,7 +751,8 @@ hipError_t launch_gemm(GemmEpi epi, const GemmArgs& a0, const Exec& ex) {
   if (a0.fold && (epi != EPI_SCALED_STORE || a0.M <= 64)) return hipErrorInvalidValue;  // row blocks of eight tiles
   const bool nt12 = (epi == EPI_SWIGLU || (epi == EPI_SCALED_STORE && a0.fold)) && a0.Wp8 == nullptr;
   const bool half_block = (epi == EPI_SCALED_STORE || epi == EPI_LOGITS_EB) && a0.Wp8 == nullptr;
-  const GemmPlan p = gemm_plan(a0.M, a0.n_tiles, a0.K, (a0.part && !a0.no_split) ? a0.part_cap : 0, nt12, half_block);
+  const GemmPlan p = gemm_plan(a0.M, a0.n_tiles, a0.K, (a0.part && !a0.no_split) ? a0.part_cap : 0, nt12, half_block,
+                               epi == EPI_SWIGLU);
   if (p.nt == 0) return hipErrorInvalidValue;
   if (p.splits > 1 && (a0.counters == nullptr || (int64_t)p.n_cb * p.m_blocks * kCtrStride > kLayerCtr0))
     return hipErrorInvalidValue;
