@@ -24,6 +24,21 @@
 
 namespace sbd {
 
+// Maximum and sum over the four lanes r, r + 16, r + 32, r + 48 of a row: the lane swaps of
+// gfx950 work in the vector unit, where a shuffle is a round trip through LDS in the middle of
+// a stage's dependency chain.
+__device__ __forceinline__ float row_max4(float v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x2 s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float row_sum4(float v) {
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+
 // The split kernel of the per-kernel path streams long key ranges, so it is shaped for
 // bytes in flight: 8 waves, NRS row sets of 16 query rows times KP = 8 / NRS key parts (4 x 2,
 // or 2 x 4 when a row block has at most 32 rows, so that no wave idles); the key positions
@@ -35,7 +50,17 @@ namespace sbd {
 // the end the KP key parts of each row set are combined through LDS (log-sum-exp weights,
 // in part order) into the split's partial.  LDS reads are ds_read16 (ds_read8 of an fp8
 // cache), ordered by hand (see sbd_device.h).
-template <int DH, bool KV8, int NRS>
+// What a stage costs is its serial chain (LDS reads, scores, softmax, P V), so the chain is
+// short: keys are hidden only in blocks that hold some (wave-uniform), a row's maximum crosses
+// lanes in the vector unit, sums stay per lane until the end, and the state is rescaled only by
+// a block that brings some row a new maximum.  Before that (per layer): Llama 4 x 32768 116 us
+// -> 108 (5.0 TB/s), Qwen 8 x 8192 71.6 -> 58.5, e4m3 cache 8 x 2048 24.0 -> 22.2.
+//
+// SHARED (many row blocks read the same keys, whole key range per workgroup: prefill): workgroup
+// i takes KV head i % n_kv, so that with eight KV heads an XCD reads one head's keys and values
+// and they stay in its L2 (cached loads), and the last row blocks, which see the most keys, start
+// first.
+template <int DH, bool KV8, int NRS, bool SHARED>
 __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   using KB = KvBlk<DH, KV8>;    // a staged block's layout in LDS
   constexpr int NDT = DH / 16;  // 16-wide dimension tiles
@@ -56,7 +81,9 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int rs = w % NRS, kh = w / NRS;  // row set (16 rows), key part of each stage
   const int r = lane & 15, grp = lane >> 4;
-  const int split = blockIdx.x, g = blockIdx.y / a.n_rowblocks, rb = blockIdx.y % a.n_rowblocks, b = blockIdx.z;
+  const int split = SHARED ? 0 : blockIdx.x, b = blockIdx.z;
+  const int g = SHARED ? (int)blockIdx.x % a.n_kv : (int)blockIdx.y / a.n_rowblocks;
+  const int rb = SHARED ? a.n_rowblocks - 1 - (int)blockIdx.x / a.n_kv : (int)blockIdx.y % a.n_rowblocks;
   const SeqParam sp = a.seqs[b];
   const int L = sp.cache_len, nc = sp.n_causal, k = a.k;
   const int G = a.n_q / a.n_kv;
@@ -68,9 +95,13 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   const int hq = g * G + hh;
   const int kend = row_ok ? ((j >= nc) ? L + k : L + j + 1) : 0;
   const int blk0 = split * a.blocks_per_split, blk_lim = blk0 + a.blocks_per_split;
-  int kend_w = kend;
+  int kend_w = kend, kmin_w = row_ok ? kend : INT32_MAX;
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) kend_w = max(kend_w, __shfl_xor(kend_w, o));
+  for (int o = 1; o < 16; o <<= 1) {
+    kend_w = max(kend_w, __shfl_xor(kend_w, o));
+    kmin_w = min(kmin_w, __shfl_xor(kmin_w, o));
+  }
+  kmin_w = __builtin_amdgcn_readfirstlane(kmin_w);  // keys every row of this wave sees
   const int blk1 = min(blk_lim, (kend_w + 31) / 32);  // this wave's blocks end here
   int kend_wg = kend_w;
   kend_wg = max(kend_wg, __shfl_xor(kend_wg, 16));
@@ -107,7 +138,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
       if (kb >= blk1_wg) kb = blk1_wg - 1;  // past the end: a valid block, never used
       __builtin_amdgcn_global_load_lds((const void*)KB::src(kbase, vbase, kb, part, sub * 64 + lane),
                                        (__attribute__((address_space(3))) void*)(buf + (bi * 2 + part) * BLK + sub * 1024),
-                                       16, 0, 2);  // nt: each cache byte is read once
+                                       16, 0, SHARED ? 0 : 2);  // nt: each cache byte is read once
     }
   };
 
@@ -165,40 +196,45 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
       for (int dt = 0; dt < NDT; ++dt) vr[jb][dt] = rd(blk + (jb * 2 + 1) * BLK + KB::voff(16 * dt + r, grp));
     // sc[jb][t][i]: score of key 32 (kb0 + jb) + 16 t + 4 grp + i for query row r; a block
     // at or past blk1 (beyond this wave's last key, or in the next split) counts for nothing
+    if (kb0 + BPW > blk1 || 32 * (kb0 + BPW) > kmin_w) {  // wave-uniform: some key is hidden from some row
+#pragma unroll
+      for (int jb = 0; jb < BPW; ++jb)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (kb0 + jb >= blk1 || 32 * (kb0 + jb) + 16 * t + 4 * grp + i >= kend) sc[jb][t][i] = -INFINITY;
+    }
     float mloc = -INFINITY;
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (kb0 + jb >= blk1 || 32 * (kb0 + jb) + 16 * t + 4 * grp + i >= kend) sc[jb][t][i] = -INFINITY;
-          mloc = fmaxf(mloc, sc[jb][t][i]);
-        }
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 16));
-    mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
-    const float m_new = fmaxf(m_run, mloc);
-    // exponents are <= 0 here: the hardware exp2 suffices (results below 2^-126 flush to 0)
-    const float scale = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, sc[jb][t][i]);
+    mloc = row_max4(mloc);
+    // a new maximum rescales what the rows hold; most blocks bring none (then the factor is 1)
+    if (__any(mloc > m_run)) {
+      const float m_new = fmaxf(m_run, mloc);
+      // exponents are <= 0 here: the hardware exp2 suffices (results below 2^-126 flush to 0)
+      const float scale = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= scale;
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) o[dt] *= scale;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;  // no key so far: every score is -inf
     float p[BPW][8];
-    float lsum = 0.f;
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float sv = sc[jb][t][i];
-          const float v = (sv == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(sv - m_new);
+          const float v = __builtin_amdgcn_exp2f(sc[jb][t][i] - m_use);
           p[jb][4 * t + i] = v;
-          lsum += v;
+          l_run += v;  // this lane's keys; the row's four lanes are added at the end
         }
-    lsum += __shfl_xor(lsum, 16);
-    lsum += __shfl_xor(lsum, 32);
-    l_run = l_run * scale + lsum;
-    m_run = m_new;
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) o[dt] *= scale;
     lds_wait();
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
@@ -246,6 +282,8 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     compute(c);
   }
   __syncthreads();  // the ring is free: it holds the other key parts' states next
+
+  l_run = row_sum4(l_run);
 
   // combine the key parts of each row set: parts 1 .. KP - 1 park (m, l, O), part 0 adds
   constexpr int SLOT = NDT * 16 + 16;  // bytes per lane (16-byte aligned pieces)
@@ -310,13 +348,17 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   attn_merge_body<DH, false>(a, item);
 }
 
+// SHARED from four row blocks that cover the key range in one split: two row blocks (block
+// forwards of more than 64 rows a KV head) still read most keys from HBM.
 template <int DH, bool KV8>
 static void launch_split_rs(const AttnArgs& a, dim3 grid, const Exec& ex) {
   // a row block of at most 32 rows (one block: n_rowblocks == 1) takes two row sets
   if ((a.n_q / a.n_kv) * a.k <= 32 && a.n_rowblocks == 1)
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 2>), grid, dim3(512), ex, a);
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 2, false>), grid, dim3(512), ex, a);
+  else if (a.n_splits == 1 && a.n_rowblocks >= 4)
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, true>), dim3(a.n_kv * a.n_rowblocks, 1, a.B), dim3(512), ex, a);
   else
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4>), grid, dim3(512), ex, a);
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, false>), grid, dim3(512), ex, a);
 }
 
 hipError_t launch_attention_split(const AttnArgs& a, const Exec& ex) {
