@@ -68,13 +68,14 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   constexpr int KP = 8 / NRS;                 // key parts
   constexpr int BLK = KB::BYTES;              // bytes of K (or of V) per 32-key block
   constexpr int BPW = KV8 ? 2 : 1;            // blocks per wave and stage
+  constexpr int RT = SHARED ? 2 : 1;          // row tiles (16 query rows) per wave
   constexpr int BPS = KP * BPW;               // blocks per stage
   constexpr int STAGE = BPS * 2 * BLK;        // K and V of the stage's blocks
   constexpr int NBUF = (128 * 1024) / STAGE > 8 ? 8 : (128 * 1024) / STAGE;
   constexpr int LPB = BLK / 1024;             // 1 KB wave-loads per part per block
   constexpr int PER_WAVE = STAGE / 1024 / 8;  // wave-loads of one wave per stage
   static_assert(NBUF >= 2 && (NBUF - 2) * PER_WAVE <= 63, "ring shape");
-  static_assert(NRS * KP == 8 && (KP - 1) * NRS * 64 * (NDT * 16 + 16) <= NBUF * STAGE, "wave shape");
+  static_assert(NRS * KP == 8 && (KP - 1) * NRS * 64 * RT * (NDT * 16 + 16) <= NBUF * STAGE, "wave shape");
   __shared__ __attribute__((aligned(16))) char smem[NBUF * STAGE];
   __shared__ int s_kend[8];
 
@@ -83,19 +84,29 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   const int r = lane & 15, grp = lane >> 4;
   const int split = SHARED ? 0 : blockIdx.x, b = blockIdx.z;
   const int g = SHARED ? (int)blockIdx.x % a.n_kv : (int)blockIdx.y / a.n_rowblocks;
-  const int rb = SHARED ? a.n_rowblocks - 1 - (int)blockIdx.x / a.n_kv : (int)blockIdx.y % a.n_rowblocks;
+  const int rb = SHARED ? (int)gridDim.x / a.n_kv - 1 - (int)blockIdx.x / a.n_kv : (int)blockIdx.y % a.n_rowblocks;
   const SeqParam sp = a.seqs[b];
   const int L = sp.cache_len, nc = sp.n_causal, k = a.k;
   const int G = a.n_q / a.n_kv;
   const int R = G * k;
-  const int rho = rb * 16 * NRS + rs * 16 + r;
-  const bool row_ok = rho < R;
-  const int hh = row_ok ? rho / k : 0;
-  const int j = row_ok ? rho % k : 0;
-  const int hq = g * G + hh;
-  const int kend = row_ok ? ((j >= nc) ? L + k : L + j + 1) : 0;
+  // row tile t of this wave: lane's row, its query head and block row, and its last key
+  bool row_ok[RT];
+  int hq[RT], jr[RT], kend[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int rho = (rb * NRS + rs) * 16 * RT + t * 16 + r;
+    row_ok[t] = rho < R;
+    hq[t] = g * G + (row_ok[t] ? rho / k : 0);
+    jr[t] = row_ok[t] ? rho % k : 0;
+    kend[t] = row_ok[t] ? ((jr[t] >= nc) ? L + k : L + jr[t] + 1) : 0;
+  }
   const int blk0 = split * a.blocks_per_split, blk_lim = blk0 + a.blocks_per_split;
-  int kend_w = kend, kmin_w = row_ok ? kend : INT32_MAX;
+  int kend_w = 0, kmin_w = INT32_MAX;
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    kend_w = max(kend_w, kend[t]);
+    kmin_w = min(kmin_w, row_ok[t] ? kend[t] : INT32_MAX);
+  }
 #pragma unroll
   for (int o = 1; o < 16; o <<= 1) {
     kend_w = max(kend_w, __shfl_xor(kend_w, o));
@@ -109,12 +120,15 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   if (lane == 0) s_kend[w] = kend_wg;
 
   // queries (B operand, hi and lo): row r, dims 32 s + 8 grp .. + 8; complete before the ring
-  i32x4 qf[NKS], ql[NKS];
-  const int64_t qoff = ((int64_t)(b * k + j) * a.n_q + hq) * DH;
+  i32x4 qf[RT][NKS], ql[RT][NKS];
 #pragma unroll
-  for (int s2 = 0; s2 < NKS; ++s2) {
-    qf[s2] = row_ok ? *(const i32x4*)(a.q + qoff + 32 * s2 + 8 * grp) : i32x4{0, 0, 0, 0};
-    ql[s2] = row_ok ? *(const i32x4*)(a.q_lo + qoff + 32 * s2 + 8 * grp) : i32x4{0, 0, 0, 0};
+  for (int t = 0; t < RT; ++t) {
+    const int64_t qoff = ((int64_t)(b * k + jr[t]) * a.n_q + hq[t]) * DH;
+#pragma unroll
+    for (int s2 = 0; s2 < NKS; ++s2) {
+      qf[t][s2] = row_ok[t] ? *(const i32x4*)(a.q + qoff + 32 * s2 + 8 * grp) : i32x4{0, 0, 0, 0};
+      ql[t][s2] = row_ok[t] ? *(const i32x4*)(a.q_lo + qoff + 32 * s2 + 8 * grp) : i32x4{0, 0, 0, 0};
+    }
   }
   vm_wait<0>();
   __syncthreads();
@@ -142,10 +156,15 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     }
   };
 
-  f32x4 o[NDT];
+  f32x4 o[RT][NDT];
+  float m_run[RT], l_run[RT];
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
+  for (int t = 0; t < RT; ++t) {
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+  }
 
   // this wave's block of stage st: scores, online softmax, O^T += V^T P^T
   auto compute = [&](int st) {
@@ -176,17 +195,20 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int s2 = 0; s2 < NKS; ++s2) lds_pin(kr[jb][t][s2]);
-    f32x4 sc[BPW][2];
+    f32x4 sc[RT][BPW][2];
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        sc[jb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s2 = 0; s2 < NKS; ++s2) {
           const i32x4 kf = widen(kr[jb][t][s2]);
-          sc[jb][t] = mfma16x16x32(kf, qf[s2], sc[jb][t]);
-          sc[jb][t] = mfma16x16x32(kf, ql[s2], sc[jb][t]);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf, qf[rt][s2], sc[rt][jb][t]);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf, ql[rt][s2], sc[rt][jb][t]);
         }
       }
     Frag vr[BPW][NDT];  // requested now: the softmax below hides their latency
@@ -194,47 +216,62 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) vr[jb][dt] = rd(blk + (jb * 2 + 1) * BLK + KB::voff(16 * dt + r, grp));
-    // sc[jb][t][i]: score of key 32 (kb0 + jb) + 16 t + 4 grp + i for query row r; a block
-    // at or past blk1 (beyond this wave's last key, or in the next split) counts for nothing
+    // sc[rt][jb][t][i]: score of key 32 (kb0 + jb) + 16 t + 4 grp + i for query row r of tile rt;
+    // a block at or past blk1 (beyond this wave's last key, or in the next split) counts for nothing
     if (kb0 + BPW > blk1 || 32 * (kb0 + BPW) > kmin_w) {  // wave-uniform: some key is hidden from some row
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int jb = 0; jb < BPW; ++jb)
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (kb0 + jb >= blk1 || 32 * (kb0 + jb) + 16 * t + 4 * grp + i >= kend[rt]) sc[rt][jb][t][i] = -INFINITY;
+    }
+    i32x4 pf[RT][BPW], pl[RT][BPW];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      float mloc = -INFINITY;
 #pragma unroll
       for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (kb0 + jb >= blk1 || 32 * (kb0 + jb) + 16 * t + 4 * grp + i >= kend) sc[jb][t][i] = -INFINITY;
-    }
-    float mloc = -INFINITY;
+          for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, sc[rt][jb][t][i]);
+      mloc = row_max4(mloc);
+      // a new maximum rescales what the rows hold; most blocks bring none (then the factor is 1)
+      if (__any(mloc > m_run[rt])) {
+        const float m_new = fmaxf(m_run[rt], mloc);
+        // exponents are <= 0 here: the hardware exp2 suffices (results below 2^-126 flush to 0)
+        const float scale = (m_run[rt] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run[rt] - m_new);
+        l_run[rt] *= scale;
 #pragma unroll
-    for (int jb = 0; jb < BPW; ++jb)
+        for (int dt = 0; dt < NDT; ++dt) o[rt][dt] *= scale;
+        m_run[rt] = m_new;
+      }
+      const float m_use = m_run[rt] == -INFINITY ? 0.f : m_run[rt];  // no key so far: every score is -inf
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int jb = 0; jb < BPW; ++jb) {
+        float p[8];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) mloc = fmaxf(mloc, sc[jb][t][i]);
-    mloc = row_max4(mloc);
-    // a new maximum rescales what the rows hold; most blocks bring none (then the factor is 1)
-    if (__any(mloc > m_run)) {
-      const float m_new = fmaxf(m_run, mloc);
-      // exponents are <= 0 here: the hardware exp2 suffices (results below 2^-126 flush to 0)
-      const float scale = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-      l_run *= scale;
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) o[dt] *= scale;
-      m_run = m_new;
-    }
-    const float m_use = m_run == -INFINITY ? 0.f : m_run;  // no key so far: every score is -inf
-    float p[BPW][8];
+          for (int i = 0; i < 4; ++i) {
+            const float v = __builtin_amdgcn_exp2f(sc[rt][jb][t][i] - m_use);
+            p[4 * t + i] = v;
+            l_run[rt] += v;  // this lane's keys; the row's four lanes are added at the end
+          }
+        // P as hi/lo bf16 (B operand): element e holds key 16*(e/4) + 4*grp + e%4.
 #pragma unroll
-    for (int jb = 0; jb < BPW; ++jb)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float v = __builtin_amdgcn_exp2f(sc[jb][t][i] - m_use);
-          p[jb][4 * t + i] = v;
-          l_run += v;  // this lane's keys; the row's four lanes are added at the end
+        for (int e = 0; e < 4; ++e) {
+          const float p0 = p[2 * e], p1 = p[2 * e + 1];
+          const uint32_t hw = pack_bf2(p0, p1);
+          pf[rt][jb][e] = (int)hw;
+          pl[rt][jb][e] = (int)pack_bf2(p0 - __uint_as_float(hw << 16), p1 - __uint_as_float(hw & 0xffff0000u));
         }
+      }
+    }
     lds_wait();
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
@@ -243,20 +280,13 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb) {
       if (kb0 + jb >= blk1) continue;  // wave-uniform
-      // P as hi/lo bf16 (B operand): element e holds key 16*(e/4) + 4*grp + e%4.
-      i32x4 pf, pl;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float p0 = p[jb][2 * e], p1 = p[jb][2 * e + 1];
-        const uint32_t hw = pack_bf2(p0, p1);
-        pf[e] = (int)hw;
-        pl[e] = (int)pack_bf2(p0 - __uint_as_float(hw << 16), p1 - __uint_as_float(hw & 0xffff0000u));
-      }
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         const i32x4 vf = widen(vr[jb][dt]);
-        o[dt] = mfma16x16x32(vf, pf, o[dt]);
-        o[dt] = mfma16x16x32(vf, pl, o[dt]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) o[rt][dt] = mfma16x16x32(vf, pf[rt][jb], o[rt][dt]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) o[rt][dt] = mfma16x16x32(vf, pl[rt][jb], o[rt][dt]);
       }
     }
   };
@@ -283,61 +313,69 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   }
   __syncthreads();  // the ring is free: it holds the other key parts' states next
 
-  l_run = row_sum4(l_run);
+#pragma unroll
+  for (int t = 0; t < RT; ++t) l_run[t] = row_sum4(l_run[t]);
 
   // combine the key parts of each row set: parts 1 .. KP - 1 park (m, l, O), part 0 adds
-  constexpr int SLOT = NDT * 16 + 16;  // bytes per lane (16-byte aligned pieces)
-  auto park_of = [&](int part) { return smem + (((part - 1) * NRS + rs) * 64 + lane) * SLOT; };
+  constexpr int SLOT = NDT * 16 + 16;  // bytes per lane and row tile (16-byte aligned pieces)
+  auto park_of = [&](int part, int t) { return smem + ((((part - 1) * NRS + rs) * RT + t) * 64 + lane) * SLOT; };
   if (kh > 0) {
-    char* park = park_of(kh);
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) *(f32x4*)(park + dt * 16) = o[dt];
-    *(float*)(park + NDT * 16) = m_run;
-    *(float*)(park + NDT * 16 + 4) = l_run;
+    for (int t = 0; t < RT; ++t) {
+      char* park = park_of(kh, t);
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt) *(f32x4*)(park + dt * 16) = o[t][dt];
+      *(float*)(park + NDT * 16) = m_run[t];
+      *(float*)(park + NDT * 16 + 4) = l_run[t];
+    }
   }
   __syncthreads();
-  if (kh > 0 || !row_ok) return;
-  float mm = m_run;
+  if (kh > 0) return;
 #pragma unroll
-  for (int part = 1; part < KP; ++part) mm = fmaxf(mm, *(const float*)(park_of(part) + NDT * 16));
-  const float s0 = (m_run == -INFINITY) ? 0.f : exp2f(m_run - mm);
+  for (int t = 0; t < RT; ++t) {
+    if (!row_ok[t]) continue;
+    float mm = m_run[t];
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt) o[dt] *= s0;
-  float ll = l_run * s0;
+    for (int part = 1; part < KP; ++part) mm = fmaxf(mm, *(const float*)(park_of(part, t) + NDT * 16));
+    const float s0 = (m_run[t] == -INFINITY) ? 0.f : exp2f(m_run[t] - mm);
 #pragma unroll
-  for (int part = 1; part < KP; ++part) {
-    const char* park = park_of(part);
-    const float mp = *(const float*)(park + NDT * 16), lp = *(const float*)(park + NDT * 16 + 4);
-    const float sp_ = (mp == -INFINITY) ? 0.f : exp2f(mp - mm);
+    for (int dt = 0; dt < NDT; ++dt) o[t][dt] *= s0;
+    float ll = l_run[t] * s0;
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) o[dt] += *(const f32x4*)(park + dt * 16) * sp_;
-    ll += lp * sp_;
-  }
-  if (a.n_splits == 1) {  // the whole key range: normalise and store the output (no merge launch)
-    const float inv = 1.0f / ll;
-    const int64_t orow = (int64_t)b * k + j;
+    for (int part = 1; part < KP; ++part) {
+      const char* park = park_of(part, t);
+      const float mp = *(const float*)(park + NDT * 16), lp = *(const float*)(park + NDT * 16 + 4);
+      const float sp_ = (mp == -INFINITY) ? 0.f : exp2f(mp - mm);
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) {
-      i32x2 hi, lo;
-      split_bf16x4(o[dt] * inv, hi, lo);
-      const int64_t dst = aoff(orow, (int64_t)hq * DH + 16 * dt + 4 * grp, (int64_t)a.n_q * DH, a.out_mtiles);
-      *(i32x2*)(a.out + dst) = hi;
-      *(i32x2*)(a.out_lo + dst) = lo;
+      for (int dt = 0; dt < NDT; ++dt) o[t][dt] += *(const f32x4*)(park + dt * 16) * sp_;
+      ll += lp * sp_;
     }
-    return;
-  }
-
-  // the split's unnormalised (max, sum, O) per row, as attn_split_body leaves them
-  const int64_t item = (int64_t)(b * k + j) * a.n_q + hq;
-  const int64_t n_items = (int64_t)a.B * k * a.n_q;
-  if (grp == 0) {
-    float* ml = a.part_ml + ((int64_t)split * n_items + item) * 2;
-    ml[0] = mm;
-    ml[1] = ll;
-  }
-  const int64_t po = ((int64_t)split * n_items + item) * DH;
+    if (a.n_splits == 1) {  // the whole key range: normalise and store the output (no merge launch)
+      const float inv = 1.0f / ll;
+      const int64_t orow = (int64_t)b * k + jr[t];
 #pragma unroll
-  for (int dt = 0; dt < NDT; ++dt) *(f32x4*)(a.part_o + po + 16 * dt + 4 * grp) = o[dt];
+      for (int dt = 0; dt < NDT; ++dt) {
+        i32x2 hi, lo;
+        split_bf16x4(o[t][dt] * inv, hi, lo);
+        const int64_t dst = aoff(orow, (int64_t)hq[t] * DH + 16 * dt + 4 * grp, (int64_t)a.n_q * DH, a.out_mtiles);
+        *(i32x2*)(a.out + dst) = hi;
+        *(i32x2*)(a.out_lo + dst) = lo;
+      }
+      continue;
+    }
+
+    // the split's unnormalised (max, sum, O) per row, as attn_split_body leaves them
+    const int64_t item = (int64_t)(b * k + jr[t]) * a.n_q + hq[t];
+    const int64_t n_items = (int64_t)a.B * k * a.n_q;
+    if (grp == 0) {
+      float* ml = a.part_ml + ((int64_t)split * n_items + item) * 2;
+      ml[0] = mm;
+      ml[1] = ll;
+    }
+    const int64_t po = ((int64_t)split * n_items + item) * DH;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) *(f32x4*)(a.part_o + po + 16 * dt + 4 * grp) = o[t][dt];
+  }
 }
 
 template <int DH>
@@ -356,7 +394,7 @@ static void launch_split_rs(const AttnArgs& a, dim3 grid, const Exec& ex) {
   if ((a.n_q / a.n_kv) * a.k <= 32 && a.n_rowblocks == 1)
     SBD_KLAUNCH((attn_split_kernel<DH, KV8, 2, false>), grid, dim3(512), ex, a);
   else if (a.n_splits == 1 && a.n_rowblocks >= 4)
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, true>), dim3(a.n_kv * a.n_rowblocks, 1, a.B), dim3(512), ex, a);
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, true>), dim3(a.n_kv * ((a.n_rowblocks + 1) / 2), 1, a.B), dim3(512), ex, a);
   else
     SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, false>), grid, dim3(512), ex, a);
 }
