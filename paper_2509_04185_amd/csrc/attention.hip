@@ -67,7 +67,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   constexpr int NKS = DH / 32;  // 32-wide reduction steps for the scores
   constexpr int KP = 8 / NRS;                 // key parts
   constexpr int BLK = KB::BYTES;              // bytes of K (or of V) per 32-key block
-  constexpr int BPW = KV8 ? 2 : 1;            // blocks per wave and stage
+  constexpr int BPW = KV8 && !SHARED ? 2 : 1;  // blocks per wave and stage
   constexpr int RT = SHARED ? 2 : 1;          // row tiles (16 query rows) per wave
   constexpr int BPS = KP * BPW;               // blocks per stage
   constexpr int STAGE = BPS * 2 * BLK;        // K and V of the stage's blocks
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[NBUF * STAGE];
   __shared__ int s_kend[8];
 
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int rs = w % NRS, kh = w / NRS;  // row set (16 rows), key part of each stage
   const int r = lane & 15, grp = lane >> 4;
   const int split = SHARED ? 0 : blockIdx.x, b = blockIdx.z;
@@ -142,15 +142,20 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   const float kv_sc = a.kv_scale;
   // Wave-load u of wave w in stage st: i = w + 8u -> block i / (2 LPB) of the stage, part
   // (i / LPB) % 2 (K, V), 1 KB slice i % LPB; pieces XOR-swizzled (KvBlk).
+  const char* src[PER_WAVE];  // of block 0: a block of K, and one of V, is BLK bytes further
+#pragma unroll
+  for (int u = 0; u < PER_WAVE; ++u) {
+    const int idx = w + 8 * u;
+    src[u] = KB::src(kbase, vbase, 0, (idx / LPB) % 2, (idx % LPB) * 64 + lane);
+  }
   auto issue = [&](int st) {
     char* buf = smem + (st % NBUF) * STAGE;
 #pragma unroll
     for (int u = 0; u < PER_WAVE; ++u) {
       const int idx = w + 8 * u;
       const int bi = idx / (2 * LPB), part = (idx / LPB) % 2, sub = idx % LPB;
-      int kb = blk0 + BPS * st + bi;
-      if (kb >= blk1_wg) kb = blk1_wg - 1;  // past the end: a valid block, never used
-      __builtin_amdgcn_global_load_lds((const void*)KB::src(kbase, vbase, kb, part, sub * 64 + lane),
+      const int kb = min(blk0 + BPS * st + bi, blk1_wg - 1);  // past the end: a valid block, never used
+      __builtin_amdgcn_global_load_lds((const void*)(src[u] + (int64_t)kb * BLK),
                                        (__attribute__((address_space(3))) void*)(buf + (bi * 2 + part) * BLK + sub * 1024),
                                        16, 0, SHARED ? 0 : 2);  // nt: each cache byte is read once
     }
@@ -166,28 +171,31 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     l_run[t] = 0.f;
   }
 
-  // this wave's block of stage st: scores, online softmax, O^T += V^T P^T
-  auto compute = [&](int st) {
+  // This wave's blocks of stage st, in two halves: scores, then online softmax and
+  // O^T += V^T P^T.  Fragments: KV8 reads 8 bytes and widens them once the reads are complete.
+  typedef typename std::conditional<KV8, i32x2, i32x4>::type Frag;
+  auto widen = [&](Frag v) -> i32x4 {
+    if constexpr (KV8) return e4m3x8_to_bf16(v, kv_sc);
+    else return v;
+  };
+  // LDS byte offsets of the lane's fragments in a stage: key 16 t + r, step s2 and dimension
+  // 16 dt + r differ from these by constants (the swizzles depend on r alone)
+  uint32_t koff[NKS];
+#pragma unroll
+  for (int s2 = 0; s2 < NKS; ++s2) koff[s2] = lds_addr(smem) + (uint32_t)(kh * BPW * 2 * BLK + KB::koff(r, s2, grp));
+  const uint32_t voff = lds_addr(smem) + (uint32_t)((kh * BPW * 2 + 1) * BLK + KB::voff(r, grp));
+  f32x4 sc[RT][BPW][2];
+  auto scores = [&](int st) {
     const int kb0 = blk0 + BPS * st + kh * BPW;  // this wave's first block
     if (kb0 >= blk1) return;  // wave-uniform: nothing of its blocks is visible to its rows
-    const char* blk = smem + (st % NBUF) * STAGE + (kh * BPW * 2) * BLK;  // block j: K at 2 j BLK, V after
-    // fragments: KV8 reads 8 bytes and widens them once the reads are complete
-    typedef typename std::conditional<KV8, i32x2, i32x4>::type Frag;
-    auto rd = [](const char* p) -> Frag {
-      if constexpr (KV8) return ds_read8(lds_addr(p));
-      else return ds_read16(lds_addr(p));
-    };
-    auto widen = [&](Frag v) -> i32x4 {
-      if constexpr (KV8) return e4m3x8_to_bf16(v, kv_sc);
-      else return v;
-    };
+    const uint32_t slot = (uint32_t)((st % NBUF) * STAGE);
     Frag kr[BPW][2][NKS];
-#pragma unroll
-    for (int jb = 0; jb < BPW; ++jb)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int s2 = 0; s2 < NKS; ++s2) kr[jb][t][s2] = rd(blk + jb * 2 * BLK + KB::koff(16 * t + r, s2, grp));
+    static_for<BPW * 2 * NKS>([&](auto I) {
+      constexpr int jb = decltype(I)::value / (2 * NKS), t = decltype(I)::value / NKS % 2, s2 = decltype(I)::value % NKS;
+      constexpr int off = jb * 2 * BLK + t * 16 * DH * KB::ES;
+      if constexpr (KV8) kr[jb][t][s2] = ds_read8<off>(koff[s2] + slot);
+      else kr[jb][t][s2] = ds_read16<off>(koff[s2] + slot);
+    });
     lds_wait();
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
@@ -195,7 +203,6 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int s2 = 0; s2 < NKS; ++s2) lds_pin(kr[jb][t][s2]);
-    f32x4 sc[RT][BPW][2];
 #pragma unroll
     for (int jb = 0; jb < BPW; ++jb)
 #pragma unroll
@@ -211,11 +218,18 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
           for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf, ql[rt][s2], sc[rt][jb][t]);
         }
       }
+  };
+  auto softmax_pv = [&](int st) {
+    const int kb0 = blk0 + BPS * st + kh * BPW;
+    if (kb0 >= blk1) return;
+    const uint32_t slot = (uint32_t)((st % NBUF) * STAGE);
     Frag vr[BPW][NDT];  // requested now: the softmax below hides their latency
-#pragma unroll
-    for (int jb = 0; jb < BPW; ++jb)
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) vr[jb][dt] = rd(blk + (jb * 2 + 1) * BLK + KB::voff(16 * dt + r, grp));
+    static_for<BPW * NDT>([&](auto I) {
+      constexpr int jb = decltype(I)::value / NDT, dt = decltype(I)::value % NDT;
+      constexpr int off = jb * 2 * BLK + dt * 16 * 32 * KB::ES;
+      if constexpr (KV8) vr[jb][dt] = ds_read8<off>(voff + slot);
+      else vr[jb][dt] = ds_read16<off>(voff + slot);
+    });
     // sc[rt][jb][t][i]: score of key 32 (kb0 + jb) + 16 t + 4 grp + i for query row r of tile rt;
     // a block at or past blk1 (beyond this wave's last key, or in the next split) counts for nothing
     if (kb0 + BPW > blk1 || 32 * (kb0 + BPW) > kmin_w) {  // wave-uniform: some key is hidden from some row
@@ -297,9 +311,17 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  for (int st = 0; st < NBUF - 1 && st < n_st; ++st) issue(st);
-  for (int c = 0; c < n_st; ++c) {
-    const int ahead = min(NBUF - 2, n_st - 1 - c);  // later stages still in flight
+  // SHARED: the two waves of a SIMD (the key parts of one row set) take turns.  Part 1 does the
+  // softmax of stage c - 1 while part 0 forms the scores of stage c and goes on a phase behind,
+  // so that one wave's products run beside the other's vector work; in step, both waited for
+  // the matrix core, then both for the vector unit.  It still reads stage c - 1, so the
+  // ring's loads go one slot less far ahead.
+  constexpr bool kLag = SHARED && KP == 2;
+  constexpr int D = kLag ? NBUF - 2 : NBUF - 1;  // stages ahead
+  static_assert(D >= 1 && D <= 7, "ring depth");
+  for (int st = 0; st < D && st < n_st; ++st) issue(st);
+  auto next_stage = [&](int c) {
+    const int ahead = min(D - 1, n_st - 1 - c);  // later stages still in flight
     if (ahead >= 6) vm_wait<6 * PER_WAVE>();
     else if (ahead == 5) vm_wait<5 * PER_WAVE>();
     else if (ahead == 4) vm_wait<4 * PER_WAVE>();
@@ -307,9 +329,17 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     else if (ahead == 2) vm_wait<2 * PER_WAVE>();
     else if (ahead == 1) vm_wait<PER_WAVE>();
     else vm_wait<0>();
-    bar();  // every wave's part of stage c is in; every wave is done with stage c - 1
-    if (c + NBUF - 1 < n_st) issue(c + NBUF - 1);
-    compute(c);
+    bar();  // every wave's part of stage c is in; every wave is done with stage c - 1 (kLag: c - 2)
+    if (c + D < n_st) issue(c + D);
+  };
+  const bool lag = kLag && kh == 1;  // wave-uniform; every wave passes n_st barriers
+  if (lag && n_st > 0) next_stage(0);
+#pragma unroll 1
+  for (int c = 0; c < n_st; ++c) {
+    if (!lag) next_stage(c);
+    scores(c);
+    if (lag && c + 1 < n_st) next_stage(c + 1);
+    softmax_pv(c);
   }
   __syncthreads();  // the ring is free: it holds the other key parts' states next
 

@@ -55,7 +55,6 @@
 
 #include <algorithm>
 #include <type_traits>
-#include <utility>
 
 #include "eb_stats.h"
 
@@ -80,16 +79,6 @@ struct MidCfg {
   static_assert(MTW >= 1 && MT % 2 == 0 && CW * WC == NT, "unsupported tile shape");
   static_assert(NS >= 3 && (NS - 1) * FPW <= 63, "vmcnt range");
 };
-
-// f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{})
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // Wait until at most n stages of FPW loads each are still in flight (n in [0, NMAX]).
 template <int FPW, int NMAX>

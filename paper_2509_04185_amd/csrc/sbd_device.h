@@ -4,6 +4,9 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "sbd_internal.h"
 
 // Launch on ex.s; the runtime records ex.start / ex.stop (when set) at the kernel's
@@ -234,6 +237,16 @@ __device__ __forceinline__ i32x2 ds_read8(uint32_t addr) {
 __device__ __forceinline__ void lds_pin(i32x2& v) { asm volatile("" : "+v"(v)); }
 // LDS byte address of a __shared__ object
 __device__ __forceinline__ uint32_t lds_addr(const void* p) { return (uint32_t)(uintptr_t)p; }
+
+// f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{})
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 __device__ __forceinline__ float wave_sum(float v) {
   v += __shfl_xor(v, 32);
