@@ -203,21 +203,28 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int s2 = 0; s2 < NKS; ++s2) lds_pin(kr[jb][t][s2]);
+    // products of one accumulator stand 2 RT (P V: 4 RT) apart, so that none waits for the last
 #pragma unroll
-    for (int jb = 0; jb < BPW; ++jb)
+    for (int jb = 0; jb < BPW; ++jb) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s2 = 0; s2 < NKS; ++s2) {
-          const i32x4 kf = widen(kr[jb][t][s2]);
+      for (int s2 = 0; s2 < NKS; ++s2) {
+        i32x4 kf[2];
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf, qf[rt][s2], sc[rt][jb][t]);
+        for (int t = 0; t < 2; ++t) {
+          kf[t] = widen(kr[jb][t][s2]);
 #pragma unroll
-          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf, ql[rt][s2], sc[rt][jb][t]);
+          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf[t], qf[rt][s2], sc[rt][jb][t]);
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) sc[rt][jb][t] = mfma16x16x32(kf[t], ql[rt][s2], sc[rt][jb][t]);
       }
+    }
   };
   auto softmax_pv = [&](int st) {
     const int kb0 = blk0 + BPS * st + kh * BPW;
@@ -295,12 +302,18 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     for (int jb = 0; jb < BPW; ++jb) {
       if (kb0 + jb >= blk1) continue;  // wave-uniform
 #pragma unroll
-      for (int dt = 0; dt < NDT; ++dt) {
-        const i32x4 vf = widen(vr[jb][dt]);
+      for (int d0 = 0; d0 < NDT; d0 += 4) {
+        i32x4 vf[4];
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) o[rt][dt] = mfma16x16x32(vf, pf[rt][jb], o[rt][dt]);
+        for (int u = 0; u < 4; ++u) {
+          vf[u] = widen(vr[jb][d0 + u]);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) o[rt][dt] = mfma16x16x32(vf, pl[rt][jb], o[rt][dt]);
+          for (int rt = 0; rt < RT; ++rt) o[rt][d0 + u] = mfma16x16x32(vf[u], pf[rt][jb], o[rt][d0 + u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) o[rt][d0 + u] = mfma16x16x32(vf[u], pl[rt][jb], o[rt][d0 + u]);
       }
     }
   };
