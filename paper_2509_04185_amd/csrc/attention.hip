@@ -56,19 +56,21 @@ __device__ __forceinline__ float row_sum4(float v) {
 // a block that brings some row a new maximum.  Before that (per layer): Llama 4 x 32768 116 us
 // -> 108 (5.0 TB/s), Qwen 8 x 8192 71.6 -> 58.5, e4m3 cache 8 x 2048 24.0 -> 22.2.
 //
-// SHARED (many row blocks read the same keys, whole key range per workgroup: prefill): workgroup
+// SRT > 0 (many row blocks read the same keys, whole key range per workgroup: prefill): workgroup
 // i takes KV head i % n_kv, so that with eight KV heads an XCD reads one head's keys and values
 // and they stay in its L2 (cached loads), and the last row blocks, which see the most keys, start
-// first.
-template <int DH, bool KV8, int NRS, bool SHARED>
+// first.  A wave takes SRT row tiles; with two, every fragment it reads feeds twice the products
+// and two chains overlap (chunks of 1024 rows, median layer: one 89.8 us, two 79.2 us).
+template <int DH, bool KV8, int NRS, int SRT>
 __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
+  constexpr bool SHARED = SRT > 0;
   using KB = KvBlk<DH, KV8>;    // a staged block's layout in LDS
   constexpr int NDT = DH / 16;  // 16-wide dimension tiles
   constexpr int NKS = DH / 32;  // 32-wide reduction steps for the scores
   constexpr int KP = 8 / NRS;                 // key parts
   constexpr int BLK = KB::BYTES;              // bytes of K (or of V) per 32-key block
   constexpr int BPW = KV8 && !SHARED ? 2 : 1;  // blocks per wave and stage
-  constexpr int RT = SHARED ? 2 : 1;          // row tiles (16 query rows) per wave
+  constexpr int RT = SHARED ? SRT : 1;        // row tiles (16 query rows) per wave
   constexpr int BPS = KP * BPW;               // blocks per stage
   constexpr int STAGE = BPS * 2 * BLK;        // K and V of the stage's blocks
   constexpr int NBUF = (128 * 1024) / STAGE > 8 ? 8 : (128 * 1024) / STAGE;
@@ -429,17 +431,22 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
   attn_merge_body<DH, false>(a, item);
 }
 
-// SHARED from four row blocks that cover the key range in one split: two row blocks (block
-// forwards of more than 64 rows a KV head) still read most keys from HBM.
+// Shared keys (SRT) from four row blocks that take the whole key range each: with fewer, most
+// keys come from HBM once all the same.  Two row tiles per wave halve the workgroups and make
+// each 1.76 times as long; largest first, one tile takes about W / 256 + 1/4 rounds for W
+// workgroups, so two pay from about 1.5 rounds.
 template <int DH, bool KV8>
 static void launch_split_rs(const AttnArgs& a, dim3 grid, const Exec& ex) {
+  const int64_t wgs = (int64_t)a.n_kv * a.n_rowblocks * a.B;
   // a row block of at most 32 rows (one block: n_rowblocks == 1) takes two row sets
   if ((a.n_q / a.n_kv) * a.k <= 32 && a.n_rowblocks == 1)
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 2, false>), grid, dim3(512), ex, a);
-  else if (a.n_splits == 1 && a.n_rowblocks >= 4)
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, true>), dim3(a.n_kv * ((a.n_rowblocks + 1) / 2), 1, a.B), dim3(512), ex, a);
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 2, 0>), grid, dim3(512), ex, a);
+  else if (a.n_splits > 1 || a.n_rowblocks < 4)
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, 0>), grid, dim3(512), ex, a);
+  else if (wgs <= kAttnCus * 3 / 2)
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, 1>), dim3(a.n_kv * a.n_rowblocks, 1, a.B), dim3(512), ex, a);
   else
-    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, false>), grid, dim3(512), ex, a);
+    SBD_KLAUNCH((attn_split_kernel<DH, KV8, 4, 2>), dim3(a.n_kv * ((a.n_rowblocks + 1) / 2), 1, a.B), dim3(512), ex, a);
 }
 
 hipError_t launch_attention_split(const AttnArgs& a, const Exec& ex) {
