@@ -53,8 +53,9 @@ __device__ __forceinline__ float row_sum4(float v) {
 // What a stage costs is its serial chain (LDS reads, scores, softmax, P V), so the chain is
 // short: keys are hidden only in blocks that hold some (wave-uniform), a row's maximum crosses
 // lanes in the vector unit, sums stay per lane until the end, and the state is rescaled only by
-// a block that brings some row a new maximum.  Before that (per layer): Llama 4 x 32768 116 us
-// -> 108 (5.0 TB/s), Qwen 8 x 8192 71.6 -> 58.5, e4m3 cache 8 x 2048 24.0 -> 22.2.
+// a block that brings some row a new maximum.  Per layer, before, with that, and with addresses
+// formed once: Llama 4 x 32768 116, 108, 98 us (5.5 TB/s), Qwen 8 x 8192 71.6, 58.5, 55.9, e4m3
+// cache 8 x 2048 24.0, 22.2, 22.3.
 //
 // SRT > 0 (many row blocks read the same keys, whole key range per workgroup: prefill): workgroup
 // i takes KV head i % n_kv, so that with eight KV heads an XCD reads one head's keys and values
