@@ -179,17 +179,20 @@ __global__ __launch_bounds__(NW * 64) void gemv_kernel(GemvArgs a) {
 
   // ---- epilogue
   if constexpr (EPI == EPI_QKV) {
-    if constexpr (NW > 1) {  // gather the group's 8 tiles in wave 0
+    // four waves share the rows (wave w: rows 4g + w); one wave alone took them one after the
+    // other at the kernel's tail (tiny decoder, 4 rows: 9.2 -> 6.7 us)
+    constexpr bool kShare = NW == 4;
+    if constexpr (NW > 1) {  // gather the group's 8 tiles in the waves that finish them
       __shared__ f32x4 fin[C][64];
 #pragma unroll
       for (int ct = 0; ct < C; ++ct)
         if (owns_tile<NW>(ct, wave)) fin[ct][lane] = acc[ct];
       __syncthreads();
-      if (wave != 0) return;
+      if (!kShare && wave != 0) return;
 #pragma unroll
       for (int ct = 0; ct < C; ++ct) acc[ct] = fin[ct][lane];
     }
-    qkv_epilogue<DH>(a.qkv, a.M, sub, acc, rinv, qpre);
+    qkv_epilogue<DH>(a.qkv, a.M, sub, acc, rinv, qpre, kShare ? wave : -1);
     return;
   } else if constexpr (EPI == EPI_LOGITS_EB) {
     static_assert(C == 8 && NW == 1, "the logits statistics take whole groups in one wave");
