@@ -430,6 +430,11 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
   int n_part_cur = d / 16;
   int* counters = c->at<int>(L.counters);
   int n_splits = pick_splits((int64_t)B * nkv * n_rb, nblocks, c->n_cu_dev);
+  // a split is at least a stage: its key parts (waves) work on a stage's blocks side by side, so
+  // that fewer blocks take no less time and only leave more partials to merge (attention.hip;
+  // tiny decoder, 4 rows on 64 keys: 3 splits and a merge 5.0 + 3.1 us, one split 4.8)
+  const int stage_blocks = (G * k <= 32 && n_rb == 1 ? 4 : 2) * (kvf.fp8 ? 2 : 1);
+  n_splits = std::min(n_splits, (nblocks + stage_blocks - 1) / stage_blocks);
   const int bps = (nblocks + n_splits - 1) / n_splits;
   n_splits = (nblocks + bps - 1) / bps;
   if (n_splits > 1 && (int64_t)n_splits * M * nq > L.attn_items)  // never (compute_layout)
