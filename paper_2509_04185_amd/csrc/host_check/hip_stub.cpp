@@ -5,9 +5,12 @@
 // that needs them is taken.
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
 #include "hip/hip_runtime.h"
 #include "sbd_internal.h"
+
+std::vector<int> g_forward_rows;  // rows of every forward enqueued so far
 
 struct ihipEvent_t {
   int unused;
@@ -69,7 +72,10 @@ hipError_t launch_gemm(GemmEpi, const GemmArgs&, const Exec&) { return hipSucces
 GemvShape gemv_pick(GemmEpi, int, int) { return GemvShape{8, 1, 2, 1}; }
 hipError_t launch_gemv(GemmEpi, const GemvArgs&, GemvShape, const Exec&) { return hipSuccess; }
 hipError_t launch_pack(const bf16_t*, const bf16_t*, bf16_t*, int64_t, int, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_embed(const EmbedArgs&, const InlineParams*, const Exec&) { return hipSuccess; }
+hipError_t launch_embed(const EmbedArgs& a, const InlineParams*, const Exec&) {
+  g_forward_rows.push_back(a.M);
+  return hipSuccess;
+}
 hipError_t launch_rope_stage(const RopeStageArgs&, const Exec&) { return hipSuccess; }
 hipError_t launch_rope_table(float*, int64_t, int, double, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_import(const KvCopyArgs&, hipStream_t) { return hipSuccess; }

@@ -4,6 +4,7 @@
 // leave the context's state unchanged; the state machine (prefill, block forward, commit,
 // reset, KV import) must move the cache lengths as documented.  Exit status 0 when every
 // check holds.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -39,6 +40,34 @@ static sbd_model_config tiny_config() {
   c.vocab = 1024; c.mask_id = 1023; c.qk_norm = 0; c.rms_eps = 1e-5f; c.rope_theta = 1e4f;
   c.max_batch = 4; c.max_seq_len = 96; c.max_block = 8; c.prefill_chunk = 0; c.weight_format = SBD_WEIGHTS_BF16;
   return c;
+}
+
+extern std::vector<int> g_forward_rows;  // hip_stub.cpp: rows of every forward enqueued
+
+// The forwards of a prompt: whole chunks and what is left.
+static void check_prefill_forwards(const sbd_model_config& tiny, const sbd_weights& w, int32_t named, int chunk) {
+  sbd_model_config c = tiny;
+  c.max_batch = 1;
+  c.max_seq_len = 8300;
+  c.prefill_chunk = named;
+  size_t bytes = 0;
+  CHECK(sbd_workspace_bytes(&c, &bytes) == SBD_OK);
+  void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+  sbd_ctx* ctx = nullptr;
+  CHECK(sbd_create(&c, &w, ws, bytes, nullptr, &ctx) == SBD_OK && ctx != nullptr);
+  const std::vector<int32_t> prompt(8300, 3);
+  for (int n : {1, 64, 127, 128, 129, 255, 256, 257, 300, 513, 1023, 1024, 1025, 1100, 2048, 2049, 2065, 5003, 7169, 7200, 8193, 8300}) {
+    if (!ctx || g_failed) break;
+    CHECK(sbd_reset(ctx, 0) == SBD_OK);
+    g_forward_rows.clear();
+    CHECK(sbd_prefill(ctx, 0, prompt.data(), n, nullptr) == SBD_OK);
+    CHECK((int)g_forward_rows.size() == (n + chunk - 1) / chunk);
+    for (size_t i = 0; i < g_forward_rows.size(); ++i)
+      CHECK(g_forward_rows[i] == std::min(chunk, n - (int)i * chunk));
+    if (g_failed) std::fprintf(stderr, "prompt of %d, chunk %d: a first forward of %d rows\n", n, chunk, g_forward_rows[0]);
+  }
+  CHECK(sbd_destroy(ctx) == SBD_OK);
+  std::free(ws);
 }
 
 int main() {
@@ -260,6 +289,9 @@ int main() {
   CHECK(sbd_destroy(ctx) == SBD_OK);
   CHECK(sbd_destroy(nullptr) == SBD_ERR_INVALID_ARG);
   std::free(ws);
+
+  check_prefill_forwards(cfg, w, 0, 1024);
+  for (int chunk : {1, 100, 128, 256, 300, 1024, 1500, 4096}) check_prefill_forwards(cfg, w, chunk, chunk);
 
   std::printf("%d of %d host checks %s\n", g_checks - g_failed, g_checks, g_failed ? "passed, some FAILED" : "passed");
   return g_failed ? 1 : 0;

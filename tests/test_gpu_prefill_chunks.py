@@ -1,7 +1,6 @@
 """Prefills on both sides of the sizes at which a chunk changes its kernels, against the oracle:
 the 256 rows past which the QKV projection adds every K step in fp32, whole and ragged row
-blocks of 128, and the 1024 rows past which a prompt takes several forwards of about the same
-size.  The logits of the last row, and keys and values at every position of both layers."""
+blocks of 128, and the 1024 rows past which a prompt takes several forwards.  The logits of the last row, and keys and values at every position of both layers."""
 import dataclasses
 
 import numpy as np
