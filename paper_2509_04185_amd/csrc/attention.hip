@@ -61,7 +61,10 @@ __device__ __forceinline__ float row_sum4(float v) {
 // i takes KV head i % n_kv, so that with eight KV heads an XCD reads one head's keys and values
 // and they stay in its L2 (cached loads), and the last row blocks, which see the most keys, start
 // first.  A wave takes SRT row tiles; with two, every fragment it reads feeds twice the products
-// and two chains overlap (chunks of 1024 rows, median layer: one 89.8 us, two 79.2 us).
+// and two chains overlap (a prompt of 4096 in chunks of 1024, per layer: one 377 us, two 342 us;
+// e4m3 cache 405 and 345).  The two waves of a SIMD go in step: one of them a phase behind the
+// other, softmax beside scores, took a ring stage and was slower (e4m3 cache 360 us against 340 us,
+// bf16 340 against 332).
 template <int DH, bool KV8, int NRS, int SRT>
 __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
   constexpr bool SHARED = SRT > 0;
@@ -327,16 +330,11 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
-  // SHARED: the two waves of a SIMD (the key parts of one row set) take turns.  Part 1 does the
-  // softmax of stage c - 1 while part 0 forms the scores of stage c and goes on a phase behind,
-  // so that one wave's products run beside the other's vector work; in step, both waited for
-  // the matrix core, then both for the vector unit.  It still reads stage c - 1, so the
-  // ring's loads go one slot less far ahead.
-  constexpr bool kLag = SHARED && KP == 2;
-  constexpr int D = kLag ? NBUF - 2 : NBUF - 1;  // stages ahead
+  constexpr int D = NBUF - 1;  // stages ahead
   static_assert(D >= 1 && D <= 7, "ring depth");
   for (int st = 0; st < D && st < n_st; ++st) issue(st);
-  auto next_stage = [&](int c) {
+#pragma unroll 1
+  for (int c = 0; c < n_st; ++c) {
     const int ahead = min(D - 1, n_st - 1 - c);  // later stages still in flight
     if (ahead >= 6) vm_wait<6 * PER_WAVE>();
     else if (ahead == 5) vm_wait<5 * PER_WAVE>();
@@ -345,16 +343,9 @@ __global__ __launch_bounds__(512) void attn_split_kernel(AttnArgs a) {
     else if (ahead == 2) vm_wait<2 * PER_WAVE>();
     else if (ahead == 1) vm_wait<PER_WAVE>();
     else vm_wait<0>();
-    bar();  // every wave's part of stage c is in; every wave is done with stage c - 1 (kLag: c - 2)
+    bar();  // every wave's part of stage c is in; every wave is done with stage c - 1
     if (c + D < n_st) issue(c + D);
-  };
-  const bool lag = kLag && kh == 1;  // wave-uniform; every wave passes n_st barriers
-  if (lag && n_st > 0) next_stage(0);
-#pragma unroll 1
-  for (int c = 0; c < n_st; ++c) {
-    if (!lag) next_stage(c);
     scores(c);
-    if (lag && c + 1 < n_st) next_stage(c + 1);
     softmax_pv(c);
   }
   __syncthreads();  // the ring is free: it holds the other key parts' states next
