@@ -624,7 +624,7 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
 
 // ---- host side: plan and launch
 
-GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool half_block, bool nt14) {
+GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool half_block, int nt14) {
   GemmPlan best{};
   const int mt = M <= 32 ? 2 : (M <= 64 ? 4 : 8);
   const int mb = (M + mt * 16 - 1) / (mt * 16);
@@ -635,9 +635,10 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
   // 384 tiles of QKV at 1024 rows (32 blocks x 8 row blocks against 24 x 8).  14-tile blocks
   // (gate/up of more than 64 rows): Llama 8B's 1792 tiles are 128 of them, 256 workgroups at
   // 256 rows where 16-tile blocks leave 32 CUs idle; gate/up at 1024 rows 367 -> 353 us, at 256
-  // rows 99.9 -> 97.0, with e4m3 weights at 128 rows 62.8 -> 60.1.  With fewer rows the stream
-  // of the weights sets the time and the split they need costs more than they gain (64 rows
-  // 48.8 -> 53.0 us, 32 rows 39.9 -> 43.7).
+  // rows 99.9 -> 97.0.  In two K slices (65 to 128 rows) they pay with e4m3 weights (128 rows
+  // 57.8 -> 55.7 us, 78 rows 54.1 -> 52.4) and not with bf16 (71.8 us against 66.7 in 16-tile
+  // blocks, 78 rows 63.1 against 59.4): the stream of the weights sets the time there, and so it
+  // does with fewer rows (64 rows 48.8 -> 53.0 us, 32 rows 39.9 -> 43.7).
   for (int nt : {16, 14, 12, 8}) {
     // half_block: 16-tile blocks also when n_tiles % 16 == 8, the last one half full (one K
     // slice: its empty half would otherwise park and sum nothing)
@@ -645,7 +646,7 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
     if ((n_tiles % nt && !half) || (nt == 12 && !nt12) || (nt == 14 && (!nt14 || mt < 8))) continue;
     const int n_cb = (n_tiles + nt - 1) / nt;
     for (int ks = 1; ks <= 8; ++ks) {
-      if (ks > 1 && (S_all / ks < 4 || half)) break;
+      if (ks > 1 && (S_all / ks < 4 || half || (nt == 14 && ks > nt14))) break;
       if (ks > 1 && (int64_t)ks * n_cb * nt * 16 * mb * mt * 16 > part_cap) break;
       if (ks > 1 && (int64_t)n_cb * mb * kCtrStride > kLayerCtr0) break;  // one counter line per unit
       // one workgroup per CU, 32 CUs per XCD; units of a column block share its XCD.  The
@@ -688,10 +689,13 @@ static void launch_cfg(const GemmArgs& a, const Exec& ex) {
       return;
     }
   }
-  if (a.splits > 1)
-    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true, false>), dim3(grid), dim3(512), ex, a);
-  else
-    SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false, false>), dim3(grid), dim3(512), ex, a);
+  if constexpr (NT != 14 || W8) {  // 14-tile blocks of bf16 weights: one K slice (gemm_plan)
+    if (a.splits > 1) {
+      SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, true, false>), dim3(grid), dim3(512), ex, a);
+      return;
+    }
+  }
+  SBD_KLAUNCH((gemm_kernel<MT, NT, EPI, W8, false, false>), dim3(grid), dim3(512), ex, a);
 }
 template <int MT, int NT, int EPI>
 static void launch_fmt(const GemmArgs& a, const Exec& ex) {
@@ -741,7 +745,7 @@ hipError_t launch_gemm(GemmEpi epi, const GemmArgs& a0, const Exec& ex) {
   const bool nt12 = (epi == EPI_SWIGLU || (epi == EPI_SCALED_STORE && a0.fold)) && a0.Wp8 == nullptr;
   const bool half_block = (epi == EPI_SCALED_STORE || epi == EPI_LOGITS_EB) && a0.Wp8 == nullptr;
   const GemmPlan p = gemm_plan(a0.M, a0.n_tiles, a0.K, (a0.part && !a0.no_split) ? a0.part_cap : 0, nt12, half_block,
-                               epi == EPI_SWIGLU);
+                               epi != EPI_SWIGLU ? 0 : (a0.Wp8 != nullptr ? 8 : 1));
   if (p.nt == 0) return hipErrorInvalidValue;
   if (p.splits > 1 && (a0.counters == nullptr || (int64_t)p.n_cb * p.m_blocks * kCtrStride > kLayerCtr0))
     return hipErrorInvalidValue;

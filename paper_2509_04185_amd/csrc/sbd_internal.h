@@ -179,10 +179,10 @@ struct GemmPlan {
 // nt12: 12-tile column blocks may be used (EPI_SWIGLU and folding EPI_SCALED_STORE with bf16
 // weights: epilogues without row reductions across the block's columns).  half_block: 16-tile blocks may be
 // used when n_tiles % 16 == 8, the last one half full (EPI_SCALED_STORE / EPI_LOGITS_EB with
-// bf16 weights; n_cb then counts it).  nt14: 14-tile blocks may be used (EPI_SWIGLU, more than
-// 64 rows).
+// bf16 weights; n_cb then counts it).  nt14: 14-tile blocks may be used in at most this many K
+// slices (EPI_SWIGLU, more than 64 rows; 0: not at all).
 GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12 = false, bool half_block = false,
-                   bool nt14 = false);
+                   int nt14 = 0);
 
 hipError_t launch_gemm(GemmEpi epi, const GemmArgs& a, const Exec& ex);
 
