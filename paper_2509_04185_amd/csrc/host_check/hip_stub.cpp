@@ -1,8 +1,8 @@
 // Host-only stand-ins for the HIP runtime calls and the kernel launchers that sbd_api.cpp
 // uses, for the sanitizer build of the C ABI's validation and state machine.  Memory calls
 // act on host memory at once (so the sanitizers check every workspace offset the API code
-// copies to or fills); launchers do nothing; the device reports no CUs, so no decode path
-// that needs them is taken.
+// copies to or fills); launchers do nothing but note a few arguments for host_check.cpp; the
+// device reports no CUs unless it is told to, so no decode path that needs them is taken.
 #include <cstdlib>
 #include <cstring>
 #include <vector>
@@ -11,6 +11,9 @@
 #include "sbd_internal.h"
 
 std::vector<int> g_forward_rows;  // rows of every forward enqueued so far
+int g_device_cus = 0;
+sbd::AttnArgs g_attention{};  // of the last split attention
+int g_merges = 0;             // merge launches so far
 
 struct ihipEvent_t {
   int unused;
@@ -61,7 +64,7 @@ hipError_t hipGetDevice(int* dev) {
   return hipSuccess;
 }
 hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t, int) {
-  *value = 0;
+  *value = g_device_cus;
   return hipSuccess;
 }
 
@@ -80,8 +83,14 @@ hipError_t launch_rope_stage(const RopeStageArgs&, const Exec&) { return hipSucc
 hipError_t launch_rope_table(float*, int64_t, int, double, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_import(const KvCopyArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_kv_export(const KvCopyArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_attention_split(const AttnArgs&, const Exec&) { return hipSuccess; }
-hipError_t launch_attention_merge(const AttnArgs&, const Exec&) { return hipSuccess; }
+hipError_t launch_attention_split(const AttnArgs& a, const Exec&) {
+  g_attention = a;
+  return hipSuccess;
+}
+hipError_t launch_attention_merge(const AttnArgs&, const Exec&) {
+  ++g_merges;
+  return hipSuccess;
+}
 bool fused_plan(FwdArgs&, int, int64_t) { return false; }
 hipError_t launch_fused_forward(const FwdArgs&, int, const Exec&) { return hipSuccess; }
 bool layer_xcd_fits(const sbd_model_config&, int, int, int) { return false; }

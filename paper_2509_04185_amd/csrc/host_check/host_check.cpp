@@ -11,7 +11,9 @@
 #include <cstring>
 #include <vector>
 
+#include "hip/hip_runtime.h"
 #include "sbd.h"
+#include "sbd_internal.h"
 
 static int g_failed = 0, g_checks = 0;
 #define CHECK(cond)                                                    \
@@ -42,7 +44,10 @@ static sbd_model_config tiny_config() {
   return c;
 }
 
-extern std::vector<int> g_forward_rows;  // hip_stub.cpp: rows of every forward enqueued
+// hip_stub.cpp: rows of every forward enqueued, the device's CUs, the last split attention, merges
+extern std::vector<int> g_forward_rows;
+extern int g_device_cus, g_merges;
+extern sbd::AttnArgs g_attention;
 
 // The forwards of a prompt: whole chunks and what is left.
 static void check_prefill_forwards(const sbd_model_config& tiny, const sbd_weights& w, int32_t named, int chunk) {
@@ -65,6 +70,60 @@ static void check_prefill_forwards(const sbd_model_config& tiny, const sbd_weigh
     for (size_t i = 0; i < g_forward_rows.size(); ++i)
       CHECK(g_forward_rows[i] == std::min(chunk, n - (int)i * chunk));
     if (g_failed) std::fprintf(stderr, "prompt of %d, chunk %d: a first forward of %d rows\n", n, chunk, g_forward_rows[0]);
+  }
+  CHECK(sbd_destroy(ctx) == SBD_OK);
+  std::free(ws);
+}
+
+// The attention's key splits on a device of 256 CUs (one workgroup each), for block forwards of
+// `heads` query heads over two KV heads: every key block in one split, no split empty, one split
+// for a range of at most two stages and never more than stages (a stage is a key block for each
+// key part: 4 parts with at most 32 query rows of a KV head, else 2; with an e4m3 cache two blocks
+// for each); a merge exactly where there are several.
+static void check_splits(const sbd_model_config& tiny, const sbd_weights& w, int heads, int kv_format) {
+  sbd_model_config c = tiny;
+  c.n_layers = 1;
+  c.n_q_heads = heads;
+  c.max_batch = 40;
+  c.max_seq_len = 4200;
+  c.max_block = 64;
+  c.kv_format = kv_format;
+  size_t bytes = 0;
+  CHECK(sbd_workspace_bytes(&c, &bytes) == SBD_OK);
+  void* ws = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+  sbd_ctx* ctx = nullptr;
+  g_device_cus = 256;
+  CHECK(sbd_create(&c, &w, ws, bytes, nullptr, &ctx) == SBD_OK && ctx != nullptr);
+  g_device_cus = 0;
+  sbd::Layout lay;
+  CHECK(sbd::compute_layout(c, &lay));
+  const std::vector<int32_t> prompt(4200, 3), toks(40 * 64, 5);
+  std::vector<int32_t> seqs(40);
+  for (int b = 0; b < 40; ++b) seqs[b] = b;
+  std::vector<float> logits(1);  // never written
+  for (int len : {1, 31, 64, 100, 127, 129, 200, 255, 256, 260, 500, 513, 1000, 2048, 4100}) {
+    for (int b = 0; ctx && b < 40; ++b) {
+      CHECK(sbd_reset(ctx, b) == SBD_OK);
+      CHECK(b % 7 != 0 || sbd_prefill(ctx, b, prompt.data(), len, nullptr) == SBD_OK);  // the others stay empty
+    }
+    for (int B : {1, 2, 3, 5, 8, 13, 17, 20, 33, 40})
+      for (int k : {1, 4, 13, 16, 17, 33, 64}) {
+        if (!ctx || g_failed) break;
+        const int merges = g_merges;
+        CHECK(sbd_block_forward(ctx, B, seqs.data(), k, toks.data(), nullptr, nullptr, nullptr, logits.data()) == SBD_OK);
+        const int R = heads / 2 * k, rb = (R + 63) / 64, W = B * 2 * rb, blocks = (len + k + 31) / 32;
+        const int stage = (R <= 32 ? 4 : 2) * (kv_format == SBD_KV_FP8_E4M3 ? 2 : 1);
+        const int s = g_attention.n_splits, bps = g_attention.blocks_per_split;
+        CHECK(s >= 1 && s <= sbd::kMaxSplits && s * bps >= blocks && (s - 1) * bps < blocks);
+        CHECK(s == 1 || (s - 1) * W < 256);
+        CHECK(s == 1 || blocks > 2 * stage);
+        CHECK(s <= (blocks + stage - 1) / stage);
+        CHECK(s == 1 || (int64_t)s * B * k * heads <= lay.attn_items);
+        CHECK((g_merges > merges) == (s > 1));
+        if (g_failed)
+          std::fprintf(stderr, "%d x %d rows, %d heads over %d keys, format %d: %d splits of %d blocks\n", B, k, heads, len,
+                       kv_format, s, bps);
+      }
   }
   CHECK(sbd_destroy(ctx) == SBD_OK);
   std::free(ws);
@@ -292,6 +351,9 @@ int main() {
 
   check_prefill_forwards(cfg, w, 0, 1024);
   for (int chunk : {1, 100, 128, 256, 300, 1024, 1500, 4096}) check_prefill_forwards(cfg, w, chunk, chunk);
+
+  for (int heads : {4, 8, 32})
+    for (int fmt : {(int)SBD_KV_BF16, (int)SBD_KV_FP8_E4M3}) check_splits(cfg, w, heads, fmt);
 
   std::printf("%d of %d host checks %s\n", g_checks - g_failed, g_checks, g_failed ? "passed, some FAILED" : "passed");
   return g_failed ? 1 : 0;

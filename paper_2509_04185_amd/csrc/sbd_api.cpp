@@ -293,7 +293,11 @@ GemvArgs gemv_base(const bf16_t* A, const bf16_t* A_lo, int64_t lda, int M, int 
 // takes 128 KB of LDS), as long as every split keeps a block.  More rounds cost a
 // workgroup's start (queries, first stage of the ring, final combine and partial store)
 // again on every CU: with ragged lengths (batch 32, 512 to 4096 positions) four splits
-// instead of one took the attention from 92 to 105 us.
+// instead of one took the attention from 92 to 105 us.  The number is rounded up, so a batch
+// that does not divide the CUs leaves some workgroups to a second round; one split fewer is
+// faster for sequences of similar lengths (Llama 8B, 5 x 8 rows over 1000 keys 21.6 against
+// 15.3 us, 20 x 8 over 2000 52.8 against 37.3) and slower where few are much longer than the
+// rest (11 x 8 over 2000 to 12000 keys 67 against 85 us, 17 x 4 128 against 156).
 int pick_splits(int64_t work_groups_per_split, int nblocks, int n_cu) {
   const int64_t target = std::min(kAttnCus, std::max(1, n_cu));
   int s = (int)std::max<int64_t>(1, (target + work_groups_per_split - 1) / work_groups_per_split);
@@ -430,11 +434,15 @@ sbd_status run_forward(sbd_ctx* c, int B, int k, const std::vector<RowParam>& ro
   int n_part_cur = d / 16;
   int* counters = c->at<int>(L.counters);
   int n_splits = pick_splits((int64_t)B * nkv * n_rb, nblocks, c->n_cu_dev);
-  // a split is at least a stage: its key parts (waves) work on a stage's blocks side by side, so
-  // that fewer blocks take no less time and only leave more partials to merge (attention.hip;
-  // tiny decoder, 4 rows on 64 keys: 3 splits and a merge 5.0 + 3.1 us, one split 4.8)
-  const int stage_blocks = (G * k <= 32 && n_rb == 1 ? 4 : 2) * (kvf.fp8 ? 2 : 1);
-  n_splits = std::min(n_splits, (nblocks + stage_blocks - 1) / stage_blocks);
+  // One split, and no merge launch, while the range is at most two stages of the split kernel's
+  // ring (attention.hip: `stage` key blocks, which its key parts work on side by side), and no
+  // more splits than stages: fewer blocks leave key parts idle and more partials to merge.
+  // Attention and merge, as the CUs alone ask and so (us): tiny decoder, 4 rows over 64 keys 8.9,
+  // 5.0, over 4000 11.1, 9.4; Llama 8B, 4 x 8 rows over 40 keys 11.8, 7.9, 240 12.4, 9.8, 260 to
+  // 1000 the same within 0.3; 1 x 32 over 40 11.7, 8.4; e4m3 cache, 4 x 8 over 240 13.1, 9.6, 500
+  // 13.1, 12.1, 520 to 1000 13.3, 13.7 (half as many splits, of whole stages: the one loss).
+  const int stage = (G * k <= 32 && n_rb == 1 ? 4 : 2) * (kvf.fp8 ? 2 : 1);
+  n_splits = nblocks <= 2 * stage ? 1 : std::min(n_splits, (nblocks + stage - 1) / stage);
   const int bps = (nblocks + n_splits - 1) / n_splits;
   n_splits = (nblocks + bps - 1) / bps;
   if (n_splits > 1 && (int64_t)n_splits * M * nq > L.attn_items)  // never (compute_layout)
