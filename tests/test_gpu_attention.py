@@ -6,8 +6,13 @@ rows) against the oracle, on the tiny decoder.
   launched.  128 sequences of ragged lengths (17 to 136 cached positions), k = 2.
 * Query rows of a KV head that fit in 32 (G k <= 32) run as 2 row sets x 4 key parts; more
   rows as 4 x 2.  Both, with several key splits, at k = 8 and k = 20 over 16 sequences.
+* Four and more row blocks per KV head with one key split share their keys: one row tile a
+  wave up to 1.5 workgroups per CU, two above.  Blocks of 64 rows and of 49 (a ragged last row
+  block) at batch 8 and 16, sequences of different lengths, causal and prediction rows mixed.
 Each with a bf16 and an e4m3 cache; every sequence is compared with the oracle.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -21,9 +26,8 @@ pytestmark = pytest.mark.gpu
 REGRESS = (5e-3, 6e-4)
 
 
-def build(kv, B, max_seq, max_block, seed):
+def build(kv, B, max_seq, max_block, seed, shape=synth.TINY):
     from paper_2509_04185_amd import Sbd
-    shape = synth.TINY
     w = synth.make_weights(shape, seed, device="cuda")
     lib = Sbd(shape, w, max_batch=B, max_seq_len=max_seq, max_block=max_block, kv_format=kv)
     fp8 = kv != "bf16"
@@ -76,4 +80,35 @@ def test_row_sets_and_splits(kv, k):
     got = lib.block_forward(list(range(B)), toks, is_mask=is_mask, n_causal=nc).cpu().numpy()
     ref = model.block_forward(caches, toks, nc).logits
     parity.close(got, ref, regress=REGRESS, label=f"{B}x{k} {kv}: ")
+    lib.close()
+
+
+# 8 KV heads of 4 query heads each: 4 row blocks of 64 rows (49 rows: the last one has 4), so
+# 32 B workgroups: 256 and 512 on 256 CUs
+@pytest.mark.parametrize("kv", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("B,k", [(8, 64), (16, 64), (8, 49), (16, 49)])
+def test_shared_keys_in_blocks(B, k, head_dim, kv):
+    print(f"[gpu] shared-key attention: {B} x {k} rows, head dim {head_dim}, {kv} cache", flush=True)
+    wide = dataclasses.replace(synth.TINY, name="shared", n_q_heads=32, n_kv_heads=8, head_dim=head_dim)
+    shape, lib, model, fp8 = build(kv, B, 400, 64, 9540 + k, wide)
+    lens = [1 + (97 * b) % 331 for b in range(B)]       # 1 .. 331 positions
+    caches = install(shape, lib, 9540 + k, lens, fp8)
+    nc = [(0, 1, k, k // 2, 33)[b % 5] for b in range(B)]
+    toks = np.full((B, k), shape.mask_id, dtype=np.int32)
+    for b in range(B):
+        toks[b, :nc[b]] = synth.make_tokens(9550 + k, max(nc), shape, stream=b)[:nc[b]]
+    is_mask = (toks == shape.mask_id).astype(np.uint8)
+    lib.profile(True)
+    lib.profile_read()
+    got = lib.block_forward(list(range(B)), toks, is_mask=is_mask, n_causal=nc)
+    prof = lib.profile_read()
+    lib.profile(False)
+    assert prof["attention"][0] == shape.n_layers and prof.get("attn_merge", (0, 0.0))[0] == 0, prof  # one key split
+    again = lib.block_forward(list(range(B)), toks, is_mask=is_mask, n_causal=nc)
+    assert torch.equal(got, again)
+    ref = model.block_forward(caches, toks, nc).logits
+    # e4m3: of the 2^19 values and more that a layer stages a few round to the other code, 1/16 of
+    # the value, which the rows of that sequence see with the weight of one key in 65 and more
+    parity.close(got.cpu().numpy(), ref, regress=(2e-2, 2e-3) if fp8 else REGRESS, label=f"{B}x{k} d_h {head_dim} {kv}: ")
     lib.close()
