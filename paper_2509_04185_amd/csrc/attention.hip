@@ -59,8 +59,10 @@ __device__ __forceinline__ float row_sum4(float v) {
 //
 // SRT > 0 (many row blocks read the same keys, whole key range per workgroup: prefill): workgroup
 // i takes KV head i % n_kv, so that with eight KV heads an XCD reads one head's keys and values
-// and they stay in its L2 (cached loads), and the last row blocks, which see the most keys, start
-// first.  A wave takes SRT row tiles; with two, every fragment it reads feeds twice the products
+// and they stay in its L2 (cached loads), and the row blocks go from the last to the first.  Rows
+// are numbered query head first, so that within each head the blocks that see the most keys start
+// before those that see fewer (not over all heads): prompts of 576 tokens 22.8 -> 18.0 us, 768
+// 33.2 -> 29.3, the same where the rounds are full.  A wave takes SRT row tiles; with two, every fragment it reads feeds twice the products
 // and two chains overlap (a prompt of 4096 in chunks of 1024, per layer: one 377 us, two 342 us;
 // e4m3 cache 405 and 345).  The two waves of a SIMD go in step: one of them a phase behind the
 // other, softmax beside scores, took a ring stage and was slower (e4m3 cache 360 us against 340 us,
@@ -424,9 +426,14 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 }
 
 // Shared keys (SRT) from four row blocks that take the whole key range each: with fewer, most
-// keys come from HBM once all the same.  Two row tiles per wave halve the workgroups and make
-// each 1.76 times as long; largest first, one tile takes about W / 256 + 1/4 rounds for W
-// workgroups, so two pay from about 1.5 rounds.
+// keys come from HBM once all the same.  Two row tiles per wave halve the workgroups and make each
+// about 1.75 times as long, so one tile is better while half the workgroups leave CUs idle.  Where
+// the two meet depends on how unequal the workgroups' ranges are, and the line at 1.5 rounds of
+// one-tile workgroups lies between what is best for each (one tile, two, us; W workgroups of one
+// tile).  Prompts from their start: 768 rows (W 384) 29.5, 32.6, 960 36.7, 39.5, 1024 42.8, 41.6;
+// 1024 rows behind 1024 78, 71.  Blocks of 64 rows, sequences of 250 to 2000 keys: 9 of them (W 288)
+// 41, 65, 14 76, 71, 20 75, 75; of 2000 keys each: 8 28, 43, 9 82, 69, 16 90, 78, 20 129, 145.  Equal
+// ranges from 1 to 1.5 rounds and from 2 to 3 would be 12 to 17 % better the other way.
 template <int DH, bool KV8>
 static void launch_split_rs(const AttnArgs& a, dim3 grid, const Exec& ex) {
   const int64_t wgs = (int64_t)a.n_kv * a.n_rowblocks * a.B;
