@@ -93,15 +93,6 @@ __device__ __forceinline__ void vm_wait_stages(int n) {
     vm_wait<0>();
   }
 }
-// Barrier between stages: LDS reads of this wave complete, then s_barrier.  The empty asm
-// statements keep the compiler from moving LDS accesses across it.
-__device__ __forceinline__ void stage_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // Value of an XCD-local counter, read with an atomic (a load could be served by the CU's own
 // L1); the zero comes from an instruction the compiler cannot see through, so the atomic
 // stays one.
@@ -191,6 +182,10 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
   const int nst = s_e - s_b;
   const int t0 = cb * NT;
 
+  // Barrier between stages.  It waits for nothing of the wave's own: a loading wave has waited for
+  // the stage that its barrier hands over, and a multiplying wave's LDS reads of a stage are
+  // complete at the lds_wait of its last row tile, before it comes to the next barrier.  The empty
+  // asm statements keep the compiler from moving LDS accesses across it.
   auto bar = [] {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -263,8 +258,8 @@ __global__ __launch_bounds__(512) void gemm_kernel(GemmArgs a) {
 
   // LDS reads of a stage with ds_read16 (sbd_device.h): the compiler would otherwise guard
   // every read of LDS with a wait for all direct loads in flight (it cannot tell the ring
-  // slots apart), draining the ring at each step.  Ordering is explicit instead: the stage
-  // barrier before the reads, a wait after them, and the results pinned behind it.  The
+  // slots apart), draining the ring at each step.  Ordering is explicit instead: the barrier
+  // before the reads, a wait after them, and the results pinned behind it.  The
   // weights of a stage are read during the stage before (two register sets), its activations
   // one row tile ahead, so LDS reads overlap the matrix work.
   constexpr int WFB = W8 ? 512 : 1024;  // bytes of one weight fragment in LDS
