@@ -93,6 +93,7 @@ __device__ __forceinline__ void vm_wait_stages(int n) {
     vm_wait<0>();
   }
 }
+
 // Value of an XCD-local counter, read with an atomic (a load could be served by the CU's own
 // L1); the zero comes from an instruction the compiler cannot see through, so the atomic
 // stays one.
@@ -654,10 +655,15 @@ GemmPlan gemm_plan(int M, int n_tiles, int K, int64_t part_cap, bool nt12, bool 
       const double m_time = steps * nt * mt * 2.0 * 16.0 / 4.0 / 2.4e9;           // MFMA issue, 4 SIMDs
       const double part_bytes = ks > 1 ? 2.0 * ks * n_tiles * 16.0 * mb * mt * 16 * 4 : 0.0;
       const double a_bytes = (double)n_cb * mb * mt * 16 * K * 4;
-      // the split's own cost (parked partials, the slices' wait, their sums): a price per slice
-      // batch fitted to the single-finisher reduction this kernel used before; on the measured
-      // shapes it still picks the faster plans (a model of the shared sums alone moved gate/up
-      // to unsplit plans that ran 0.5 % slower per forward)
+      // The split's own cost (parked partials, the slices' wait, their sums): a price per batch of
+      // slices, fitted to an earlier kernel in which one workgroup added them all, and kept.  Every
+      // plan of every projection of both 8B shapes on this kernel, 32 to 1024 rows, both weight
+      // formats: the pick is within 3 % of the fastest but for (us, the pick and the fastest) e4m3
+      // gate/up at 32 rows, whose weights the model prices at two bytes (8 tiles 31.0, 16 in two
+      // slices 26.4; Qwen 29.5, 25.7), Qwen's down projection in 8 slices instead of 7 (32 rows
+      // 25.0, 23.4, 64 rows 30.2, 28.1), O at 512 and 1024 rows (16 tiles in 4 slices 41.4, 8 in two
+      // 40.4, e4m3 40.2, 37.6; 16 in two 65.4, 8 in one 62.3, e4m3 64.6, 60.0) and e4m3 QKV at 512
+      // (16 in two 64.9, 8 in one 62.9).
       const int nacc = (mt / 2) * (nt / 2);  // accumulator tiles per wave (2 x 2 waves)
       const int zb = nacc >= 32 ? 1 : (nacc >= 16 ? 2 : 4);
       const double reduce = ks > 1 ? 1e-6 + 0.6e-6 * ((ks + zb - 1) / zb) : 0.0;
