@@ -1,10 +1,10 @@
-"""The GEMM of more than 16 rows at the edges of its tiles, against the oracle.
+"""The GEMM of more than 16 rows at the edges of its row blocks, against the oracle.
 
 Row counts on both sides of its row blocks (32, 64, 128 rows, several blocks of 128) and
-ragged inside a 16-row tile, on a two-layer decoder whose projections split K 1 to 8 ways
-(d 1024: 32 K steps; ffn 2816: 88 steps, which 8 slices share unevenly) and whose vocabulary
-(136 tiles) ends in a half-full 16-tile block.  bf16 and e4m3 weights; logits, and the block
-step's statistics against the selection on the same logits.
+ragged inside a 16-row tile, on a two-layer decoder whose projections all run as 8-tile column
+blocks, K whole or in 2 to 8 slices (d 1024: 32 K steps; ffn 2816: 88 steps, which 6 slices
+share unevenly).  Wider blocks are in test_gpu_gemm_plans.py.  bf16 and e4m3 weights; logits,
+and the block step's statistics against the selection on the same logits.
 """
 import dataclasses
 

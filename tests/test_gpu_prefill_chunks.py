@@ -1,6 +1,8 @@
 """Prefills on both sides of the sizes at which a chunk changes its kernels, against the oracle:
 the 256 rows past which the QKV projection adds every K step in fp32, whole and ragged row
-blocks of 128, and the 1024 rows past which a prompt takes several forwards.  The logits of the last row, and keys and values at every position of both layers."""
+blocks of 128, and the 1024 rows past which a prompt takes several forwards.  The logits of the
+last row, and keys and values at every position of both layers.  The projections of this narrow
+decoder mostly run as 8-tile column blocks; wider ones are in test_gpu_gemm_plans.py."""
 import dataclasses
 
 import numpy as np
@@ -13,7 +15,6 @@ from oracle import sbd_oracle as O
 
 pytestmark = pytest.mark.gpu
 
-# 96 QKV tiles: blocks of 16, 12 and 8 tiles all divide them
 SHAPE = dataclasses.replace(synth.TINY_QK, name="chunks", d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64,
                             ffn_dim=2816, vocab=2176, mask_id=2175)
 N_MAX = 2100
@@ -53,7 +54,7 @@ def test_prefill_sizes(model, n):
         parity.close(logits.cpu().numpy(), ref.reshape(-1), label="logits: ")
 
 
-# 8 KV heads: from 513 rows the attention's workgroups take the whole key range of one or (past
+# 8 KV heads: from 497 rows the attention's workgroups take the whole key range, with one or (past
 # 768 rows) two row tiles a wave; with small chunks it takes key splits of one tile a wave.
 @pytest.mark.parametrize("head_dim,kv", [(64, "bf16"), (64, "fp8_e4m3"), (128, "bf16"), (128, "fp8_e4m3")])
 def test_attention_forms_agree(head_dim, kv):
