@@ -48,10 +48,10 @@ def step_bytes(shape, lens, k, wbytes=2, kvbytes=2):
     return fwd, eb
 
 
-def gate_up_bytes(shape, M):
-    """Algorithmic bytes of one gate/up launch: both weight matrices, the bf16 input rows,
-    the bf16 SwiGLU output rows."""
-    return 2 * 2 * shape.ffn_dim * shape.d_model + 2 * M * shape.d_model + 2 * M * shape.ffn_dim
+def gate_up_bytes(shape, M, wbytes=2):
+    """Algorithmic bytes of one gate/up launch: both weight matrices (wbytes per element), the
+    bf16 input rows, the bf16 SwiGLU output rows."""
+    return wbytes * 2 * shape.ffn_dim * shape.d_model + 2 * M * shape.d_model + 2 * M * shape.ffn_dim
 
 
 def layer_mlp_bytes(shape, M, wbytes=2):
@@ -376,7 +376,7 @@ def main():
             kind, bpl = "layer_mlp", layer_mlp_bytes(s, B * k, wbytes)
             label = "layer_mlp_kernel (gate/up + SwiGLU + down + residual, per-XCD)"
         else:
-            kind, bpl = "gate_up", gate_up_bytes(s, B * k)
+            kind, bpl = "gate_up", gate_up_bytes(s, B * k, wbytes)
             if B * k <= 16:
                 label = "gemv_kernel<…, EPI_SWIGLU> (gate/up projection + SwiGLU, decode-sized GEMM)"
             else:
